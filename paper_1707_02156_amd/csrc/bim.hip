@@ -93,7 +93,6 @@ void launch_leg_mfma(hipStream_t st, int nbatch, int maxrows, const void *batche
                      double *out, long NC);
 int leg_mfma_max_rows();
 int leg_mfma_max_depth();
-size_t fk_lds_bytes(int p, int qs, bool sl, int tg);
 void launch_fk(hipStream_t st, bool sl, bool dl, int p, int qs, int nt, const double *Gx, const double *Gd, long NC6,
                const double *wsing, const double *cs, const double *X0, double *part, double *Fa, long NC12);
 void launch_sum_part(hipStream_t st, int nt, int Q1, int nk, int P1, const double *part, const PipeDrops &pd, int u0,
@@ -2000,7 +1999,7 @@ static Ctx::PipeTab &pipe_tables(Ctx &c, int p, int qs)
 static bool pipe_fits(int p, int qs)
 {
     return 2 * (qs + 1) <= leg_mfma_max_rows() && (p + 1) <= leg_mfma_max_depth() &&
-           (qs + 1) <= leg_mfma_max_depth() && fk_lds_bytes(p, qs, true, 4) <= 163840 && rot_lds_bytes(p) <= 163840;
+           (qs + 1) <= leg_mfma_max_depth() && rot_lds_bytes(p) <= 163840;
 }
 
 // Singular pass of a group of drops of one degree (and singular grid) through

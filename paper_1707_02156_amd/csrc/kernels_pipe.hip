@@ -23,6 +23,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 namespace bim {
@@ -224,20 +225,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 }
 
 // ----------------------------------------------------------------------------
-// FK: Fourier sums and kernels. Block: TG consecutive targets x one rotated
+// FK: Fourier sums and kernels. Item: 16 consecutive targets x one rotated
 // latitude j'. Gx rows: j' (Ptilde) and Q1 + j' (d/dtheta); Gd row j'.
 // SL: partial[t][j'][3] += omega W (f/r + xh (xh.f)/r^3) summed over the longitudes.
 // DL: Fa^mu[j'][t*12 + pair*2 + {cos, sin}] of the six stresslet fields.
+//
+// The Fourier sums are contractions on v_mfma_f64_4x4x4 (four blocks of 4x4x4:
+// 4 rows x 16 columns x depth 4, the granule that wastes least for 9 to 28
+// rows) with the symmetries of the longitudes folded in: with the even and odd
+// orders and the cosine and sine sums apart, row kk <= qs/2 gives the points
+// kk, kk + qs, -kk and qs - kk, a quarter of the plain product's work. Columns
+// are the item's 16 targets, so the three components of x, x_theta, x_phi and
+// f at a point meet in one lane, which evaluates the pole rule at its points
+// and holds the folded stresslet values as operand rows of the analysis.
+//
+// A wavefront takes two row tiles: each LDS read feeds both, and the 48 or 24
+// independent products of a step cover its latency (one tile per wavefront at
+// four wavefronts per SIMD read twice as much and waited: 2.26 ms against 2.05
+// at the size below). A block (2 to 4 wavefronts, 79 KB of LDS at p = 48, two
+// per CU) walks over items; the slab of G that is summed next is on its way
+// into the other LDS buffer by 16-byte direct loads meanwhile.
+//
+// Bound: the FP64 pipe, which the matrix instructions share with the vector
+// ones (10000 of some 13500 cycles per wavefront and item are products), then
+// HBM. One launch over 15053 targets of degree 48: single layer 3.67 -> 2.05 ms
+// (loads alone 1.16 ms, 4.5 TB/s; sums alone 1.55 ms); both layers over 9408
+// targets 3.36 -> 2.18 ms; against the thread-per-point recurrences before it.
 // ----------------------------------------------------------------------------
-// point records of 12 fields padded to an odd number of doubles, so that
-// lanes reading consecutive points hit distinct LDS banks
-constexpr int kVS = 13;
-// Each target's block of point records starts 6 doubles (12 banks) further
-// round the LDS banks than the previous one: the Fourier-analysis stage reads
-// the same point of up to 4 targets x 6 stresslet fields in one instruction,
-// and with blocks a multiple of 32 doubles apart (2 qs 13 is, for even qs)
-// those 24 reads fell on 6 bank pairs.
-__host__ __device__ inline long fk_vt(int nk) { return (long)nk * kVS + ((6 - (long)nk * kVS % 32) % 32 + 32) % 32; }
 
 // 1/sqrt(x) to full double precision: hardware estimate plus one third-order
 // correction (relative error of the estimate e -> O(e^3))
@@ -248,316 +262,441 @@ __device__ inline double rsq_full(double x)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-template <bool SL, bool DL, int TG, int FQ>
-__global__ __launch_bounds__(256) void k_fk(int p, int qs, int nt, const double *__restrict__ Gx,
-                                            const double *__restrict__ Gd, long NC6,
-                                            const double *__restrict__ wsing, const double *__restrict__ cs,
-                                            const double *__restrict__ X0, double *__restrict__ part,
-                                            double *__restrict__ Fa, long NC12)
+constexpr int kFkT = 16;        // targets per item
+constexpr int kFkMaxWaves = 4;  // wavefronts per block (two row tiles each): qs <= 62
+
+__host__ __device__ inline int fk_waves(int qs) { return (qs / 2 + 8) / 8; }      // of two tiles of 4 rows kk = 0..qs/2
+__host__ __device__ inline int fk_order_steps(int p) { return (p / 2 + 4) / 4; }  // of 4 even and 4 odd orders
+
+// LDS of a block, in doubles: cos and sin of pi e / qs, two buffers (each a
+// slab of G or a third of the analysis operand, whichever is larger), the
+// pole values of the item's targets, the single layer's sums per wavefront.
+__host__ __device__ inline int fk_buf(int p, int qs, bool dl)
+{
+    const int slab = (p + 1) * kFkT * 6, third = dl ? fk_waves(qs) * 8 * 2 * kFkT * 4 : 0;
+    return slab > third ? slab : third;
+}
+
+// threadIdx.x that the compiler takes for a new value at each call: what is
+// derived from it is formed again where it is used instead of held in
+// registers over the kernel's loop (no register is left at four wavefronts per
+// SIMD, and a spill's reload would wait for the direct loads in flight).
+__device__ inline int fk_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// x mod n for 0 <= x < 2^12, 4 <= n < 2^7 (rn = 2^20 / n + 1)
+__device__ inline int fk_mod(int x, int n, int rn) { return x - (x * rn >> 20) * n; }
+
+// One 16-byte direct load per active lane: lane l's 16 bytes at g go to LDS at
+// dst + 16 l. Written out because the compiler would wait for every direct
+// load before any later LDS read; it has no result register, and fk_staged
+// waits for it.
+__device__ inline void fk_load_lds(const double *g, const double *dst)
+{
+    const unsigned at = __builtin_amdgcn_readfirstlane(
+        (unsigned)(unsigned long)(const __attribute__((address_space(3))) double *)dst);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(g) : "m0", "memory");
+}
+
+// Rows src[mu * ld] (mu <= p), the 96 doubles of 16 targets from t0 on
+// (targets past the last one repeat it), into the LDS slab [mu][16][6] by
+// direct loads: a row is one instruction of 48 lanes.
+__device__ inline void fk_stage(const double *__restrict__ src, long ld, int P1, int t0, int nt, int w, int nw,
+                                double *slab)
+{
+    const int lane = fk_tid() & 63;
+    if (lane < 48) {
+        const double *g = src + (min(t0 + lane / 3, nt - 1) * 6 + lane % 3 * 2) + w * ld;
+        for (int mu = w; mu < P1; mu += nw, g += nw * ld) fk_load_lds(g, slab + mu * kFkT * 6);
+    }
+}
+
+// the direct loads of this wavefront are in LDS, then those of the whole block
+__device__ inline void fk_staged()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// all but the last n direct loads of this wavefront are in LDS (0 <= n <= 16),
+// then those of the whole block
+__device__ inline void fk_staged_but(int n)
+{
+    switch (n) {
+#define FK_WAIT(k) case k: asm volatile("s_waitcnt vmcnt(" #k ")" ::: "memory"); break;
+        FK_WAIT(1) FK_WAIT(2) FK_WAIT(3) FK_WAIT(4) FK_WAIT(5) FK_WAIT(6) FK_WAIT(7) FK_WAIT(8)
+        FK_WAIT(9) FK_WAIT(10) FK_WAIT(11) FK_WAIT(12) FK_WAIT(13) FK_WAIT(14) FK_WAIT(15) FK_WAIT(16)
+#undef FK_WAIT
+    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __syncthreads();
+}
+
+// Cosine and sine sums over the even and odd orders of three components, for
+// the row tiles u = 0, 1 of wavefront w: C[u][c][0], C[u][c][1] the cosine sums
+// of the even and odd orders, C[u][c][2], C[u][c][3] the sine sums, at row kk =
+// 8w + 4u + lane / 16 and target lane % 16; PHI: also those of the derivative
+// in phi, (i mu) g, in D. The table operand (rows 8w + 4u + lane % 4, orders 8s
+// + 2 (lane / 16) and the next) starts from the LDS table cs (nk entries) and
+// turns by eight orders from step to step.
+template <bool PHI>
+__device__ inline void fk_sums(int p, int KS, int w, const double2 *cs, int nk, int rn, const double *slab,
+                               double (&C)[2][3][4], double (&D)[2][3][4])
+{
+    const int lane = fk_tid() & 63, t = lane & 15, k4 = lane >> 4;
+    double ce[2], se[2], co[2], so[2], c8[2], s8[2], fm = 2.0 * k4;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int ka = 8 * w + 4 * u + (lane & 3);
+        const double2 te = cs[fk_mod(2 * k4 * ka, nk, rn)], to = cs[fk_mod((2 * k4 + 1) * ka, nk, rn)],
+                      t8 = cs[fk_mod(8 * ka, nk, rn)];
+        ce[u] = 2.0 * te.x;
+        se[u] = 2.0 * te.y;
+        co[u] = 2.0 * to.x;
+        so[u] = 2.0 * to.y;
+        c8[u] = t8.x;
+        s8[u] = t8.y;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                C[u][c][q] = 0.0;
+                if (PHI) D[u][c][q] = 0.0;
+            }
+    }
+    // the sums of component c over one step's even (e) and odd (o) orders
+    auto add = [&](int c, double2 e, double2 o, const double *ae, const double *be, const double *ao, const double *bo,
+                   const double *pae, const double *pbe, const double *pao, const double *pbo, bool odd) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            C[u][c][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(ae[u], e.x, C[u][c][0], 0, 0, 0);
+            C[u][c][2] = __builtin_amdgcn_mfma_f64_4x4x4f64(be[u], e.y, C[u][c][2], 0, 0, 0);
+            if (PHI) {
+                D[u][c][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(pae[u], e.y, D[u][c][0], 0, 0, 0);
+                D[u][c][2] = __builtin_amdgcn_mfma_f64_4x4x4f64(pbe[u], e.x, D[u][c][2], 0, 0, 0);
+            }
+        }
+        if (odd)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                C[u][c][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(ao[u], o.x, C[u][c][1], 0, 0, 0);
+                C[u][c][3] = __builtin_amdgcn_mfma_f64_4x4x4f64(bo[u], o.y, C[u][c][3], 0, 0, 0);
+                if (PHI) {
+                    D[u][c][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(pao[u], o.y, D[u][c][1], 0, 0, 0);
+                    D[u][c][3] = __builtin_amdgcn_mfma_f64_4x4x4f64(pbo[u], o.x, D[u][c][3], 0, 0, 0);
+                }
+            }
+    };
+    const double *g = slab + (2 * k4 * kFkT + t) * 6, *z = slab + t * 6;
+    // the last step's orders may lie past p: their table entries are zeroed,
+    // their operand is any row of the slab
+    const int le = 8 * (KS - 1) + 2 * k4;
+    const bool ve = le <= p, vo = le < p;
+    // a component's operands of the next step are read as soon as this step's
+    // are consumed: a whole step of products covers the LDS latency
+    double2 e[3], o[3];
+    {
+        const double *ge = KS > 1 || ve ? g : z, *go = KS > 1 || vo ? g + kFkT * 6 : z;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            e[c] = *reinterpret_cast<const double2 *>(ge + 2 * c);
+            o[c] = *reinterpret_cast<const double2 *>(go + 2 * c);
+        }
+    }
+    double pae[2], pbe[2], pao[2], pbo[2];
+#pragma unroll 1
+    for (int s = 1; s < KS; ++s) {
+        const double *n = g + 8 * kFkT * 6;
+        const double *ne = s + 1 < KS || ve ? n : z, *no = s + 1 < KS || vo ? n + kFkT * 6 : z;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            pae[u] = -fm * ce[u];
+            pbe[u] = fm * se[u];
+            pao[u] = -(fm + 1.0) * co[u];
+            pbo[u] = (fm + 1.0) * so[u];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            add(c, e[c], o[c], ce, se, co, so, pae, pbe, pao, pbo, true);
+            __builtin_amdgcn_sched_barrier(0);
+            e[c] = *reinterpret_cast<const double2 *>(ne + 2 * c);
+            o[c] = *reinterpret_cast<const double2 *>(no + 2 * c);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        g = n;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const double xe = fma(ce[u], c8[u], -(se[u] * s8[u])), xo = fma(co[u], c8[u], -(so[u] * s8[u]));
+            se[u] = fma(se[u], c8[u], ce[u] * s8[u]);
+            so[u] = fma(so[u], c8[u], co[u] * s8[u]);
+            ce[u] = xe;
+            co[u] = xo;
+        }
+        if (PHI) fm += 8.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        ce[u] = ve ? ce[u] : 0.0;
+        se[u] = ve ? se[u] : 0.0;
+        co[u] = vo ? co[u] : 0.0;
+        so[u] = vo ? so[u] : 0.0;
+        pae[u] = -fm * ce[u];
+        pbe[u] = fm * se[u];
+        pao[u] = -(fm + 1.0) * co[u];
+        pbo[u] = (fm + 1.0) * so[u];
+    }
+    const bool odd = 8 * (KS - 1) < p;  // an odd order is left (uniform)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) add(c, e[c], o[c], ce, se, co, so, pae, pbe, pao, pbo, odd);
+    // order 0 counts once
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) C[u][c][0] -= z[2 * c];
+}
+
+// The sums of one component to its values at the points kk, kk + qs, -kk and
+// qs - kk: the odd orders change sign from phi to phi + pi, the sine sums from
+// phi to -phi.
+__device__ inline void fk_points(double (&C)[4])
+{
+    const double em = C[0] - C[2], om = C[1] - C[3], ep = C[0] + C[2], op = C[1] + C[3];
+    C[0] = em + om;
+    C[1] = em - om;
+    C[2] = ep + op;
+    C[3] = ep - op;
+}
+
+template <bool SL, bool DL>
+__global__ __launch_bounds__(64 * kFkMaxWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fk(
+    int p, int qs, int nt, int ntb, const double *__restrict__ Gx, const double *__restrict__ Gd, long NC6,
+    const double *__restrict__ wsing, const double *__restrict__ cst, const double *__restrict__ X0,
+    double *__restrict__ part, double *__restrict__ Fa, long NC12)
 {
     extern __shared__ double sm[];
-    const int P1 = p + 1, Q1 = qs + 1, nk = 2 * qs;
-    const int jr = blockIdx.y;
-    const int t0 = blockIdx.x * TG;
-    const int ntg = min(TG, nt - t0);
-    // sG[tg][mu][type 0..3][c][re,im] ; type 0 x, 1 x_theta, 2 x_phi (= i mu x), 3 density
-    constexpr int NTY = SL ? 4 : 3;
-    double *sG = sm;
-    const long gsz = (long)TG * P1 * NTY * 6;
-    const long VT = fk_vt(nk);
-    double *V = sG + gsz;                    // [tg][k'][kVS] at tg VT: 12 fields, padded
-    double *sCS = V + (long)TG * VT + TG * 3;  // cos, sin of pi e / qs, e < 2 qs
-    for (int e = threadIdx.x; e < 2 * nk; e += 256) sCS[e] = cs[e];
-    // ---- load G (weights w_mu applied; x_phi built from x). All loads of a
-    // thread are issued before the first LDS store (P1 <= 52: at most 5
-    // rounds of 3 values), so the block waits for one memory latency.
-    constexpr int kGR = (52 * TG * 6 + 255) / 256;
-    double lx[kGR], lt[kGR], ld[kGR];
+    const int P1 = p + 1, Q1 = qs + 1, nk = 2 * qs, KS = fk_order_steps(p), rn = (1 << 20) / nk + 1;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    double2 *cs = reinterpret_cast<double2 *>(sm);
+    double *bA = sm + 2 * nk, *bB = bA + fk_buf(p, qs, DL), *x0 = bB + fk_buf(p, qs, DL), *red = x0 + 3 * kFkT;
+    for (int e = threadIdx.x; e < nk; e += blockDim.x) cs[e] = make_double2(cst[e], cst[nk + e]);
+    const long ldx = 2L * Q1 * NC6, ldd = (long)Q1 * NC6;
+    // pole values of 16 targets from t0 on (3 nt is even; values past the last
+    // target are not used)
+    auto stage_pole = [&](int t0) {
+        const int lane = fk_tid() & 63;
+        if (w == 0 && lane < 24) fk_load_lds(X0 + min(t0 * 3 + 2 * lane, 3 * nt - 2), x0);
+    };
+    int item = blockIdx.x;
+    __syncthreads();  // cs (its loads come before the direct loads in the count of fk_staged_but)
+    fk_stage(Gx + item / ntb * NC6, ldx, P1, item % ntb * kFkT, nt, w, nw, bA);
+    stage_pole(item % ntb * kFkT);
+    fk_stage(Gx + (Q1 + item / ntb) * NC6, ldx, P1, item % ntb * kFkT, nt, w, nw, bB);
+    const int ntot = ntb * Q1, nrow = (P1 - w + nw - 1) / nw;  // rows of a slab this wavefront loads
+    while (true) {
+        const int jr = item / ntb, t0 = item % ntb * kFkT;
+        const int next = item + gridDim.x, tn = next % ntb * kFkT;
+        const bool more = next < ntot;
+        // every slab is loaded while the one before it is summed
+        fk_staged_but(nrow);  // x in bA (x_theta still on its way to bB)
+        double x[2][3][4], N[2][3][4], xt[2][3][4];
+        fk_sums<true>(p, KS, w, cs, nk, rn, bA, x, N);
+        fk_staged();  // x_theta in bB, every wavefront through with x
+        if (SL)
+            fk_stage(Gd + jr * NC6, ldd, P1, t0, nt, w, nw, bA);
+        else if (more)
+            fk_stage(Gx + next / ntb * NC6, ldx, P1, tn, nt, w, nw, bA);
+        fk_sums<false>(p, KS, w, cs, nk, rn, bB, xt, xt);
+        // the pole rule up to the density: unit vectors h / r (in x), the single
+        // layer's weight omega |N| / r (Wr) and the stresslet's -6 omega (h.N) / r^3
+        // (sc) at this lane's points kk, kk + qs (which exist once on every row kk
+        // <= qs / 2) and -kk, qs - kk (except on the rows of phi = 0 and pi / 2)
+        const double om = wsing[jr];
+        double Wr[2][4], sc[2][4];
+        {
+            const int lane = fk_tid() & 63, t = lane & 15;
+            const double X[3] = {x0[3 * t], x0[3 * t + 1], x0[3 * t + 2]};
 #pragma unroll
-    for (int u = 0; u < kGR; ++u) {
-        const int i = threadIdx.x + 256 * u;
-        lx[u] = lt[u] = ld[u] = 0.0;
-        if (i < P1 * ntg * 6) {
-            const int e = i % 6, r = i / 6;
-            const int tg = r % ntg, mu = r / ntg;
-            const long colx = (long)(t0 + tg) * 6 + e;
-            lx[u] = Gx[((long)mu * 2 * Q1 + jr) * NC6 + colx];
-            lt[u] = Gx[((long)mu * 2 * Q1 + Q1 + jr) * NC6 + colx];
-            if (SL) ld[u] = Gd[((long)mu * Q1 + jr) * NC6 + colx];
-        }
-    }
+            for (int u = 0; u < 2; ++u) {
+                const int kk = 8 * w + 4 * u + (lane >> 4);
+                const bool one = kk <= qs / 2, two = one && kk != 0 && 2 * kk != qs;
 #pragma unroll
-    for (int u = 0; u < kGR; ++u) {
-        const int i = threadIdx.x + 256 * u;
-        if (i < P1 * ntg * 6) {
-            const int e = i % 6;           // c*2 + re/im
-            const int r = i / 6;
-            const int tg = r % ntg, mu = r / ntg;
-            const double w = mu ? 2.0 : 1.0;
-            double *g = sG + ((long)(tg * P1 + mu) * NTY) * 6;
-            g[e] = w * lx[u];
-            g[6 + e] = w * lt[u];
-            if (SL) g[18 + e] = w * ld[u];
-        }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < P1 * ntg * 3; i += 256) {
-        const int c = i % 3;
-        const int r = i / 3;
-        const int tg = r % ntg, mu = r / ntg;
-        double *g = sG + ((long)(tg * P1 + mu) * NTY) * 6;
-        // (i mu) (gr + i gi) = (-mu gi) + i (mu gr)
-        g[12 + 2 * c] = -mu * g[2 * c + 1];
-        g[12 + 2 * c + 1] = mu * g[2 * c];
-    }
-    __syncthreads();
-    const bool even = (qs & 1) == 0;
-    const int nkk = even ? qs / 2 + 1 : qs;
-    // ---- F: point values. cos/sin(mu phi) by the three-term recurrence
-    // c_{mu+1} = 2 cos(phi) c_mu - c_{mu-1} (same for sin), error O(p^2 eps).
-    // A thread takes the points kk and kk + H of one (target, component): each
-    // G value read from LDS feeds both.
-    const int H = (nkk + 1) / 2;
-    for (int it = threadIdx.x; it < ntg * H * 3; it += 256) {
-        const int c = it % 3;
-        const int r = it / 3;
-        const int kp = r % H, tg = r / H;
-        const int kq[2] = {kp, kp + H};
-        const bool two = kp + H < nkk;
-        const double *g = sG + (long)tg * P1 * NTY * 6 + 2 * c;
-        double tc[2], c0[2], s0[2], cm1[2], sm1[2];
-        double CE[2][NTY], CO[2][NTY], SE[2][NTY], SO[2][NTY];
+                for (int c = 0; c < 3; ++c) {
+                    fk_points(N[u][c]);
+                    fk_points(xt[u][c]);
+                    fk_points(x[u][c]);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int kb = min(kq[b], nkk - 1);
-            const double c1 = sCS[kb], s1 = sCS[nk + kb];
-            tc[b] = 2.0 * c1;
-            c0[b] = 1.0;
-            s0[b] = 0.0;
-            cm1[b] = c1;  // orders mu and mu - 1
-            sm1[b] = -s1;
-#pragma unroll
-            for (int q = 0; q < NTY; ++q) { CE[b][q] = 0; CO[b][q] = 0; SE[b][q] = 0; SO[b][q] = 0; }
-        }
-        // Two register sets of G values (orders mu, mu + 1), filled alternately:
-        // the next two orders are read while the current ones are summed.
-        // Indexes are clamped to p; values past the last order are never used.
-        double ac[NTY], as[NTY], aoc[NTY], aos[NTY], bc[NTY], bs[NTY], boc[NTY], bos[NTY];
-        auto gload = [&](int m, double *gc, double *gs) {
-            const double *gm = g + (long)m * NTY * 6;
-#pragma unroll
-            for (int q = 0; q < NTY; ++q) { gc[q] = gm[6 * q]; gs[q] = gm[6 * q + 1]; }
-        };
-        // orders mu (even) and mu + 1 (odd) added; the recurrences advance by two
-        auto step = [&](const double *ec, const double *es, const double *oc, const double *os) {
-#pragma unroll
-            for (int q = 0; q < NTY; ++q)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    CE[b][q] = fma(ec[q], c0[b], CE[b][q]);
-                    SE[b][q] = fma(es[q], s0[b], SE[b][q]);
-                }
-            double c1n[2], s1n[2];
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                c1n[b] = fma(tc[b], c0[b], -cm1[b]);
-                s1n[b] = fma(tc[b], s0[b], -sm1[b]);
-            }
-#pragma unroll
-            for (int q = 0; q < NTY; ++q)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    CO[b][q] = fma(oc[q], c1n[b], CO[b][q]);
-                    SO[b][q] = fma(os[q], s1n[b], SO[b][q]);
+                    for (int q = 0; q < 4; ++q) x[u][c][q] = X[c] - x[u][c][q];
                 }
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                cm1[b] = c1n[b];
-                sm1[b] = s1n[b];
-                c0[b] = fma(tc[b], c1n[b], -c0[b]);
-                s0[b] = fma(tc[b], s1n[b], -s0[b]);
-            }
-        };
-        auto last_even = [&](const double *ec, const double *es) {
+                for (int q = 0; q < 4; ++q) {
+                    const double ok = (q < 2 ? one : two) ? 1.0 : 0.0;
+                    double(&h)[3][4] = x[u];
+                    const double n0 = xt[u][1][q] * N[u][2][q] - xt[u][2][q] * N[u][1][q];
+                    const double n1 = xt[u][2][q] * N[u][0][q] - xt[u][0][q] * N[u][2][q];
+                    const double n2 = xt[u][0][q] * N[u][1][q] - xt[u][1][q] * N[u][0][q];
+                    const double r2 = h[0][q] * h[0][q] + h[1][q] * h[1][q] + h[2][q] * h[2][q];
+                    const double ri = rsq_full(r2);
 #pragma unroll
-            for (int q = 0; q < NTY; ++q)
+                    for (int c = 0; c < 3; ++c) h[c][q] *= ri;
+                    if (SL) {
+                        const double nn = n0 * n0 + n1 * n1 + n2 * n2;
+                        Wr[u][q] = ok * om * (nn * rsq_full(nn)) * ri;
+                    }
+                    if (DL) {
+                        const double hn = h[0][q] * n0 + h[1][q] * n1 + h[2][q] * n2;
+                        sc[u][q] = ok * -6.0 * om * hn * (ri * ri);
+                    }
+                    // formed here, not after the sums of f, so that x_theta and
+                    // x_phi are not held over them
 #pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    CE[b][q] = fma(ec[q], c0[b], CE[b][q]);
-                    SE[b][q] = fma(es[q], s0[b], SE[b][q]);
-                }
-        };
-        gload(0, ac, as);
-        gload(min(1, p), aoc, aos);
-        int mu = 0;
-#pragma unroll 1
-        for (; mu + 3 <= p; mu += 4) {
-            gload(mu + 2, bc, bs);
-            gload(mu + 3, boc, bos);
-            __builtin_amdgcn_sched_barrier(0);
-            step(ac, as, aoc, aos);
-            __builtin_amdgcn_sched_barrier(0);
-            gload(min(mu + 4, p), ac, as);
-            gload(min(mu + 5, p), aoc, aos);
-            __builtin_amdgcn_sched_barrier(0);
-            step(bc, bs, boc, bos);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // the set a holds orders mu and mu + 1 (clamped)
-        if (mu + 1 <= p) {
-            step(ac, as, aoc, aos);
-            mu += 2;
-            if (mu <= p) {
-                gload(mu, bc, bs);
-                last_even(bc, bs);
-            }
-        } else if (mu <= p) {
-            last_even(ac, as);
-        }
-        double *Vb = V + (long)tg * VT;
-        // value(phi) = (CE - SE) + (CO - SO); at -phi the sine terms flip; at phi + pi the odd orders flip
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            if (b == 1 && !two) break;
-            const int kk = kq[b];
-            auto put = [&](int kpt, double f1, double f2) {
-                double *v = Vb + (long)kpt * kVS;
-                v[c] = (CE[b][0] - f1 * SE[b][0]) + f2 * (CO[b][0] - f1 * SO[b][0]);
-                v[3 + c] = (CE[b][1] - f1 * SE[b][1]) + f2 * (CO[b][1] - f1 * SO[b][1]);
-                v[6 + c] = (CE[b][2] - f1 * SE[b][2]) + f2 * (CO[b][2] - f1 * SO[b][2]);
-                if (SL) v[9 + c] = (CE[b][3] - f1 * SE[b][3]) + f2 * (CO[b][3] - f1 * SO[b][3]);
-            };
-            put(kk, 1.0, 1.0);
-            put(kk + qs, 1.0, -1.0);
-            if (even && kk != 0 && kk != qs / 2) {
-                put(nk - kk, -1.0, 1.0);
-                put(qs - kk, -1.0, -1.0);
-            }
-        }
-    }
-    __syncthreads();
-    // ---- K: kernels
-    const double om = wsing[jr];
-    for (int it = threadIdx.x; it < ((ntg * nk + 63) & ~63); it += 256) {
-        const bool ok = it < ntg * nk;
-        const int tg = ok ? it / nk : 0;
-        double *v = V + (long)tg * VT + (long)(ok ? it % nk : 0) * kVS;
-        const int t = t0 + tg;
-        double e0 = 0.0, e1 = 0.0, e2 = 0.0;
-        if (ok) {
-            const double xt0 = v[3], xt1 = v[4], xt2 = v[5];
-            const double xp0 = v[6], xp1 = v[7], xp2 = v[8];
-            const double N0 = xt1 * xp2 - xt2 * xp1;
-            const double N1 = xt2 * xp0 - xt0 * xp2;
-            const double N2 = xt0 * xp1 - xt1 * xp0;
-            const double h0 = X0[3 * t] - v[0], h1 = X0[3 * t + 1] - v[1], h2 = X0[3 * t + 2] - v[2];
-            const double r2 = h0 * h0 + h1 * h1 + h2 * h2;
-            const double ri = rsq_full(r2);
-            if (SL) {
-                const double f0 = v[9], f1 = v[10], f2 = v[11];
-                const double hf = h0 * f0 + h1 * f1 + h2 * f2;
-                const double n2 = N0 * N0 + N1 * N1 + N2 * N2;
-                const double Wr = om * (n2 * rsq_full(n2)) * ri;
-                const double q = hf * ri * ri;
-                e0 = Wr * fma(h0, q, f0);
-                e1 = Wr * fma(h1, q, f1);
-                e2 = Wr * fma(h2, q, f2);
-            }
-            if (DL) {
-                const double hn = h0 * N0 + h1 * N1 + h2 * N2;
-                const double r2i = ri * ri;
-                const double sc = -6.0 * om * hn * r2i * r2i * ri;
-                v[0] = sc * h0 * h0;
-                v[1] = sc * h0 * h1;
-                v[2] = sc * h0 * h2;
-                v[3] = sc * h1 * h1;
-                v[4] = sc * h1 * h2;
-                v[5] = sc * h2 * h2;
-            }
-        }
-        if (SL && ok) {  // f is read; its slots take the point's contribution
-            v[9] = e0;
-            v[10] = e1;
-            v[11] = e2;
-        }
-    }
-    __syncthreads();
-    if (SL) {
-        // sums over the longitudes in a fixed order (run to run identical):
-        // 16 lanes per (target, component), lane l adds the points l, l + 16,
-        // ..., then a butterfly over the 16 lanes
-        for (int i0 = 0; i0 < ntg * 48; i0 += 256) {
-            const int i = i0 + threadIdx.x;
-            const bool act = i < ntg * 48;
-            const int g = act ? i >> 4 : 0, l = i & 15;
-            const int tg = g / 3, cc = g % 3;
-            double sum = 0.0;
-            if (act)
-                for (int k = l; k < nk; k += 16) sum += V[(long)tg * VT + (long)k * kVS + 9 + cc];
-            for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 16);
-            if (act && l == 0) part[((long)(t0 + tg) * Q1 + jr) * 3 + cc] = sum;
-        }
-    }
-    if (DL) {
-        // ---- FA: Fourier analysis of the six stresslet fields. One item = FQ
-        // orders of one parity (mu = base + 2q), sharing the symmetric
-        // combinations of the four points kk, -kk, kk + qs, qs - kk; FQ is
-        // the smallest that lets one pass of the block's threads take every
-        // item (a second, mostly idle pass would cost a whole item's time).
-        const int nE = p / 2 + 1, nO = (p + 1) / 2;
-        const int NGe = (nE + FQ - 1) / FQ, NG = NGe + (nO + FQ - 1) / FQ;
-        for (int it = threadIdx.x; it < NG * ntg * 6; it += 256) {
-            const int pr = it % 6;
-            const int r = it / 6;
-            const int tg = r % ntg, gidx = r / ntg;
-            const bool odd = gidx >= NGe;
-            const int base = odd ? 2 * FQ * (gidx - NGe) + 1 : 2 * FQ * gidx;
-            const double sg = odd ? -1.0 : 1.0;
-            const double *Vb = V + (long)tg * VT + pr;
-            double tq[FQ], cq[FQ], sq[FQ], cp[FQ], sp[FQ], fc[FQ], fs[FQ];
-#pragma unroll
-            for (int q = 0; q < FQ; ++q) {
-                const int mu = min(base + 2 * q, p);
-                const double c1 = sCS[mu], s1 = sCS[nk + mu];
-                tq[q] = 2.0 * c1;
-                cq[q] = 1.0;
-                sq[q] = 0.0;
-                cp[q] = c1;
-                sp[q] = -s1;
-                fc[q] = 0.0;
-                fs[q] = 0.0;
-            }
-            for (int kk = 0; kk < nkk; ++kk) {
-                const double K1 = Vb[(long)kk * kVS];
-                const double K3 = Vb[(long)(kk + qs) * kVS];
-                double K2 = 0.0, K4 = 0.0;
-                if (even && kk != 0 && kk != qs / 2) {
-                    K2 = Vb[(long)(nk - kk) * kVS];
-                    K4 = Vb[(long)(qs - kk) * kVS];
-                }
-                const double A = fma(sg, K3 + K4, K1 + K2);
-                const double Bv = fma(sg, K3 - K4, K1 - K2);
-#pragma unroll
-                for (int q = 0; q < FQ; ++q) {
-                    fc[q] = fma(cq[q], A, fc[q]);
-                    fs[q] = fma(sq[q], Bv, fs[q]);
-                    const double cn = fma(tq[q], cq[q], -cp[q]), sn = fma(tq[q], sq[q], -sp[q]);
-                    cp[q] = cq[q];
-                    sp[q] = sq[q];
-                    cq[q] = cn;
-                    sq[q] = sn;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < FQ; ++q) {
-                const int mu = base + 2 * q;
-                if (mu <= p) {
-                    double *o = Fa + ((long)mu * Q1 + jr) * NC12 + (long)(t0 + tg) * 12 + pr * 2;
-                    o[0] = fc[q];
-                    o[1] = fs[q];
+                    for (int c = 0; c < 3; ++c) asm volatile("" : "+v"(h[c][q]));
+                    if (SL) asm volatile("" : "+v"(Wr[u][q]));
+                    if (DL) asm volatile("" : "+v"(sc[u][q]));
                 }
             }
         }
+        if (SL)
+            fk_staged();  // f in bA, every wavefront through with x_theta
+        else
+            __syncthreads();
+        if (SL) {
+            if (more) fk_stage(Gx + next / ntb * NC6, ldx, P1, tn, nt, w, nw, bB);
+            double f[2][3][4];
+            fk_sums<false>(p, KS, w, cs, nk, rn, bA, f, f);
+            double e0 = 0.0, e1 = 0.0, e2 = 0.0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) fk_points(f[u][c]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double hf = x[u][0][q] * f[u][0][q] + x[u][1][q] * f[u][1][q] + x[u][2][q] * f[u][2][q];
+                    e0 = fma(Wr[u][q], fma(x[u][0][q], hf, f[u][0][q]), e0);
+                    e1 = fma(Wr[u][q], fma(x[u][1][q], hf, f[u][1][q]), e1);
+                    e2 = fma(Wr[u][q], fma(x[u][2][q], hf, f[u][2][q]), e2);
+                }
+            }
+            // sums over the longitudes in a fixed order: the tiles' rows by a
+            // butterfly, the wavefronts in turn
+            const int lane = fk_tid() & 63, t = lane & 15;
+            e0 += __shfl_xor(e0, 16, 64);
+            e1 += __shfl_xor(e1, 16, 64);
+            e2 += __shfl_xor(e2, 16, 64);
+            e0 += __shfl_xor(e0, 32, 64);
+            e1 += __shfl_xor(e1, 32, 64);
+            e2 += __shfl_xor(e2, 32, 64);
+            if (lane < kFkT) {
+                red[(w * kFkT + t) * 3] = e0;
+                red[(w * kFkT + t) * 3 + 1] = e1;
+                red[(w * kFkT + t) * 3 + 2] = e2;
+            }
+        }
+        if (DL) {
+            const int lane = fk_tid() & 63, t = lane & 15, k4 = lane >> 4;
+            // the analysis operand of two fields at a time, in the buffer that
+            // the next item's x_theta (SL: this item's f) leaves free
+            double2 *vA = reinterpret_cast<double2 *>(SL ? bA : bB), *vB = vA + nw * 8 * 2 * kFkT;
+#pragma unroll
+            for (int third = 0; third < 3; ++third) {
+                __syncthreads();  // the buffer's last contents are read
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) {
+                        // pairs (0,0) (0,1) (0,2) (1,1) (1,2) (2,2)
+                        constexpr int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {0, 1, 2, 1, 2, 2};
+                        const int a = pa[2 * third + f], b = pb[2 * third + f];
+                        const double k0 = sc[u][0] * x[u][a][0] * x[u][b][0], k1 = sc[u][1] * x[u][a][1] * x[u][b][1];
+                        const double k2 = sc[u][2] * x[u][a][2] * x[u][b][2], k3 = sc[u][3] * x[u][a][3] * x[u][b][3];
+                        const int at = ((8 * w + 4 * u + k4) * 2 + f) * kFkT + t;
+                        vA[at] = make_double2((k0 + k2) + (k1 + k3), (k0 + k2) - (k1 + k3));  // cosine: even, odd orders
+                        vB[at] = make_double2((k0 - k2) + (k1 - k3), (k0 - k2) - (k1 - k3));  // sine
+                    }
+                __syncthreads();
+                if (16 * w <= p) {
+                    // table operand: rows the orders 2 ka and 2 ka + 1, ka = 8w + 4u +
+                    // lane % 4, depth kk = 4s + lane / 16, turned from step to step
+                    double F[2][2][4], ce[2], se[2], co[2], so[2];
+                    double2 de[2], dd[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int ka = 8 * w + 4 * u + (lane & 3);
+                        const double2 te = cs[fk_mod(2 * ka * k4, nk, rn)], to = cs[fk_mod((2 * ka + 1) * k4, nk, rn)];
+                        de[u] = cs[fk_mod(8 * ka, nk, rn)];
+                        dd[u] = cs[fk_mod(8 * ka + 4, nk, rn)];
+                        ce[u] = te.x;
+                        se[u] = te.y;
+                        co[u] = to.x;
+                        so[u] = to.y;
+#pragma unroll
+                        for (int f = 0; f < 2; ++f)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) F[u][f][q] = 0.0;
+                    }
+                    const int steps = qs / 8 + 1;  // rows kk <= qs / 2 by fours
+                    for (int s = 0; s < steps; ++s) {
+#pragma unroll
+                        for (int f = 0; f < 2; ++f) {
+                            const int at = ((4 * s + k4) * 2 + f) * kFkT + t;
+                            const double2 a = vA[at], b = vB[at];
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                F[u][f][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(ce[u], a.x, F[u][f][0], 0, 0, 0);
+                                F[u][f][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(co[u], a.y, F[u][f][1], 0, 0, 0);
+                                F[u][f][2] = __builtin_amdgcn_mfma_f64_4x4x4f64(se[u], b.x, F[u][f][2], 0, 0, 0);
+                                F[u][f][3] = __builtin_amdgcn_mfma_f64_4x4x4f64(so[u], b.y, F[u][f][3], 0, 0, 0);
+                            }
+                        }
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const double xe = fma(ce[u], de[u].x, -(se[u] * de[u].y));
+                            const double xo = fma(co[u], dd[u].x, -(so[u] * dd[u].y));
+                            se[u] = fma(se[u], de[u].x, ce[u] * de[u].y);
+                            so[u] = fma(so[u], dd[u].x, co[u] * dd[u].y);
+                            ce[u] = xe;
+                            co[u] = xo;
+                        }
+                    }
+                    if (t0 + t < nt) {
+                        double *o = Fa + (long)jr * NC12 + (long)(t0 + t) * 12 + 4 * third;
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const int me = 2 * (8 * w + 4 * u + k4), mo = me + 1;
+#pragma unroll
+                            for (int f = 0; f < 2; ++f) {
+                                if (me <= p)
+                                    *reinterpret_cast<double2 *>(o + (long)me * Q1 * NC12 + 2 * f) =
+                                        make_double2(F[u][f][0], F[u][f][2]);
+                                if (mo <= p)
+                                    *reinterpret_cast<double2 *>(o + (long)mo * Q1 * NC12 + 2 * f) =
+                                        make_double2(F[u][f][1], F[u][f][3]);
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();  // f, or the analysis operand, is read; the sums per wavefront are there
+        const int tid = fk_tid();
+        if (SL && tid < 3 * kFkT) {
+            const int tt = tid / 3, c = tid % 3;
+            double s = 0.0;
+            for (int v = 0; v < nw; ++v) s += red[(v * kFkT + tt) * 3 + c];
+            if (t0 + tt < nt) part[((long)(t0 + tt) * Q1 + jr) * 3 + c] = s;
+        }
+        if (!more) break;
+        stage_pole(tn);
+        fk_stage(Gx + (Q1 + next / ntb) * NC6, ldx, P1, tn, nt, w, nw, SL ? bA : bB);
+        if (SL) {  // the next item's x is in bB
+            double *b = bA;
+            bA = bB;
+            bB = b;
+        }
+        item = next;
     }
 }
 
@@ -678,12 +817,8 @@ void pipe_set_lds_limits()
 {
     static std::once_flag once;
     std::call_once(once, [] {
-        for (const void *fn : {(const void *)k_fk<true, true, 4, 2>, (const void *)k_fk<true, true, 4, 3>,
-                               (const void *)k_fk<true, true, 4, 4>, (const void *)k_fk<true, true, 4, 5>,
-                               (const void *)k_fk<true, true, 4, 7>, (const void *)k_fk<true, false, 4, 4>,
-                               (const void *)k_fk<false, true, 4, 2>, (const void *)k_fk<false, true, 4, 3>,
-                               (const void *)k_fk<false, true, 4, 4>, (const void *)k_fk<false, true, 4, 5>,
-                               (const void *)k_fk<false, true, 4, 7>})
+        for (const void *fn : {(const void *)k_fk<true, true>, (const void *)k_fk<true, false>,
+                               (const void *)k_fk<false, true>})
             (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
     });
 }
@@ -725,47 +860,25 @@ void launch_leg_mfma(hipStream_t st, int nbatch, int maxrows, const void *batche
 int leg_mfma_max_rows() { return 7 * 16; }
 int leg_mfma_max_depth() { return 52; }
 
-size_t fk_lds_bytes(int p, int qs, bool sl, int tg)
-{
-    const int nty = sl ? 4 : 3;
-    return ((size_t)tg * (p + 1) * nty * 6 + (size_t)tg * fk_vt(2 * qs) + (size_t)tg * 3 + 4 * (size_t)qs) *
-           sizeof(double);
-}
-
+// Blocks of one launch: as many as the device holds at once (by LDS and by two
+// wavefronts per SIMD), each taking every gridDim.x-th item, so that an item's
+// first loads run under the item before.
 void launch_fk(hipStream_t st, bool sl, bool dl, int p, int qs, int nt, const double *Gx, const double *Gd, long NC6,
                const double *wsing, const double *cs, const double *X0, double *part, double *Fa, long NC12)
 {
-    constexpr int TG = 4;
-    const dim3 grid(cdiv(nt, TG), qs + 1);
-    const size_t lds = fk_lds_bytes(p, qs, sl, TG);
-    // orders per item of the stresslet analysis: the smallest with every item
-    // in one pass of the 256 threads
-    const int nE = p / 2 + 1, nO = (p + 1) / 2;
-    int fq = 7;
-    for (int q : {2, 3, 4, 5, 7})
-        if (((nE + q - 1) / q + (nO + q - 1) / q) * TG * 6 <= 256) {
-            fq = q;
-            break;
-        }
-    auto go = [&](auto fqc) {
-        constexpr int FQ = decltype(fqc)::value;
-        if (sl && dl)
-            hipLaunchKernelGGL((k_fk<true, true, TG, FQ>), grid, dim3(256), lds, st, p, qs, nt, Gx, Gd, NC6, wsing, cs,
-                               X0, part, Fa, NC12);
-        else if (sl)
-            hipLaunchKernelGGL((k_fk<true, false, TG, 4>), grid, dim3(256), lds, st, p, qs, nt, Gx, Gd, NC6, wsing, cs,
-                               X0, part, Fa, NC12);
-        else
-            hipLaunchKernelGGL((k_fk<false, true, TG, FQ>), grid, dim3(256), lds, st, p, qs, nt, Gx, Gd, NC6, wsing, cs,
-                               X0, part, Fa, NC12);
+    const int nw = fk_waves(qs), ntb = (nt + kFkT - 1) / kFkT;
+    const size_t lds = (4 * (size_t)qs + 2 * fk_buf(p, qs, dl) + 3 * kFkT + (sl ? nw * kFkT * 3 : 0)) * sizeof(double);
+    const long items = (long)ntb * (qs + 1), cus = 256, per = std::min<long>(163840 / lds, 8 / nw);
+    const dim3 grid((unsigned)std::min(items, cus * per)), block(64 * nw);
+    auto go = [&](auto fn) {
+        hipLaunchKernelGGL(fn, grid, block, lds, st, p, qs, nt, ntb, Gx, Gd, NC6, wsing, cs, X0, part, Fa, NC12);
     };
-    switch (fq) {
-    case 2: go(std::integral_constant<int, 2>()); break;
-    case 3: go(std::integral_constant<int, 3>()); break;
-    case 4: go(std::integral_constant<int, 4>()); break;
-    case 5: go(std::integral_constant<int, 5>()); break;
-    default: go(std::integral_constant<int, 7>()); break;
-    }
+    if (sl && dl)
+        go(k_fk<true, true>);
+    else if (sl)
+        go(k_fk<true, false>);
+    else
+        go(k_fk<false, true>);
 }
 
 void launch_sum_part(hipStream_t st, int nt, int Q1, int nk, int P1, const double *part, const PipeDrops &pd, int u0,
