@@ -65,6 +65,8 @@ void launch_pair_pack32(hipStream_t st, int kind, const void *jobs, int njobs, i
                         const double *cb, float4 *rec);
 void launch_pair_gather(hipStream_t st, int nt, int tile, const int *tile_of, const int *toff, const int *tent,
                         const int *off, const int *ent, const double *part, double *out, long ostride, bool add);
+void launch_mutual(hipStream_t st, int kind, int n, const MutualWork *work, int R, const PairSrc &g, double *part);
+void launch_mutual_gather(hipStream_t st, int nt, const MutualGather &mg, const double *part, double *out, long ostride);
 struct SingArgs {
     int p, qs, nt;
     const double *Ap, *Am, *ApT, *AmT;
@@ -159,6 +161,9 @@ void launch_fmm_l2p(hipStream_t st, int njobs, const FmmTgtJob *jobs, int maxn, 
                     const double2 *L, double2 *C, const double *tx, long tstride, double *out, long ostride);
 
 static const double kPi = 3.14159265358979323846;
+
+// Doubles of the static scratch of the no-allocation entry point (256 MiB)
+constexpr size_t kScratchDoubles = (size_t)1 << 25;
 
 struct Error {
     int code;
@@ -319,6 +324,17 @@ struct Ctx {
     // target of each tile
     std::vector<int> tile_of_h, tile_start_h;
     DBuf tile_of;
+    // mutual drop pairs (kernels_mutual.hip): drop i's targets against drop j's
+    // sources, i < j, both ways; blocks of targets and runs of sources of each drop
+    struct Mutual {
+        std::vector<std::pair<int, int>> pairs;  // empty: none
+        int R = 0, nblk = 0, nrun = 0;           // sources per item at most; blocks and runs over all drops
+        std::vector<int> tb, sr;                 // block and run of each target
+        std::vector<std::vector<std::pair<int, int>>> blk, run;  // of each drop: (first node, nodes)
+        std::vector<int> blk0, run0;             // first block and run of each drop
+        long items = 0;
+        DBuf dtb, dsr;
+    } mut;
     struct WList {
         std::vector<double> wt;
         // stale: built for earlier regions; refilled in place (its buffers
@@ -330,6 +346,11 @@ struct Ctx {
         HVec<PairWork> h_items;
         HVec<double> h_nw;
         HVec<FmmPair> h_fp;
+        HVec<MutualWork> h_mut;
+        HVec<int> h_moff[2], h_ment[2];  // slots of the mutual items: per block of targets, per run of sources
+        DBuf mut, moff[2], ment[2];
+        int nmut = 0;
+        double mpairs = 0.0;             // target-source pairs of the mutual items per application
         DBuf d;
         int n = 0;           // items: whole tiles first, then the remainder items
         double pairs = 0.0;  // target-source pairs per application
@@ -1125,6 +1146,122 @@ static void fmm_setup(Ctx &c, const std::vector<double> &cb0, const std::vector<
     HIPC(hipStreamSynchronize(c.stream));
 }
 
+// Plan of the mutual pairs among the drop pairs i < j of one system for which
+// `mutual` holds: the longest run of sources per item with at least three
+// rounds of blocks on the device (three blocks a CU; longer runs write fewer
+// partial sums and shorter ones balance the last round: 16 drops of degree 48,
+// double layer: 3.50 ms at 2048 sources, 3.26 at 1024, 3.38 at 512), down to
+// 256. With fewer than one round of blocks even then, or with partial
+// sums above the no-allocation scratch, there are none and every pair takes
+// k_pair, which fills the device from fewer pairs.
+template <class F> static void mutual_plan(Ctx &c, F &&mutual)
+{
+    Ctx::Mutual &M = c.mut;
+    M.pairs.clear();
+    M.items = 0;
+    if (c.opt.precision != BIM_PREC_FP64) return;
+    for (int i = 0; i < c.nd; ++i)
+        for (int j = i + 1; j < c.nd; ++j)
+            if (c.sys_h[i] == c.sys_h[j] && mutual(i, j)) M.pairs.emplace_back(i, j);
+    if (M.pairs.empty()) return;
+    auto blocks = [&](int i) { return (npts(c.drops[i].p) + kMutTargets - 1) / kMutTargets; };
+    auto count = [&](int R) {
+        long n = 0;
+        for (auto &pr : M.pairs) n += (long)blocks(pr.first) * ((npts(c.drops[pr.second].p) + R - 1) / R);
+        return n;
+    };
+    constexpr long kRound = 3 * 256;
+    for (int R : {4096, 2048, 1024, 768, 512, 384, 256}) {
+        M.R = R;
+        if (count(R) >= 3 * kRound) break;
+    }
+    M.items = count(M.R);
+    if (M.items < kRound || (double)M.items * 3 * (kMutTargets + M.R) > (double)kScratchDoubles) {
+        M.pairs.clear();
+        M.items = 0;
+        return;
+    }
+    // blocks and runs of each drop, as even as whole units of 64 targets and 16 sources allow
+    M.blk.assign(c.nd, {});
+    M.run.assign(c.nd, {});
+    M.blk0.assign(c.nd, 0);
+    M.run0.assign(c.nd, 0);
+    M.tb.resize(c.T);
+    M.sr.resize(c.T);
+    M.nblk = M.nrun = 0;
+    for (int i = 0; i < c.nd; ++i) {
+        const int n = npts(c.drops[i].p), t0 = (int)c.drops[i].toff;
+        auto split = [&](int parts, int unit, std::vector<std::pair<int, int>> &out, std::vector<int> &of, int &next) {
+            const int len = ((n + parts - 1) / parts + unit - 1) / unit * unit;
+            for (int a = 0; a < n; a += len, ++next) {
+                out.emplace_back(t0 + a, std::min(len, n - a));
+                for (int t = a; t < std::min(n, a + len); ++t) of[t0 + t] = next;
+            }
+        };
+        M.blk0[i] = M.nblk;
+        M.run0[i] = M.nrun;
+        split(blocks(i), 64, M.blk[i], M.tb, M.nblk);
+        split((n + M.R - 1) / M.R, 16, M.run[i], M.sr, M.nrun);
+    }
+    M.items = 0;
+    for (auto &pr : M.pairs) M.items += (long)M.blk[pr.first].size() * M.run[pr.second].size();
+    auto up = [&](DBuf &d, const std::vector<int> &h) {
+        d.ensure(h.size() * sizeof(int));
+        HIPC(hipMemcpyAsync(d.ptr, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice, c.stream));
+    };
+    up(M.dtb, M.tb);
+    up(M.dsr, M.sr);
+}
+
+// Items and reduction lists of the mutual pairs for a weight table.
+static void mutual_list(Ctx &c, const std::vector<double> &wt, Ctx::WList &e)
+{
+    const Ctx::Mutual &M = c.mut;
+    e.nmut = 0;
+    e.mpairs = 0.0;
+    if (M.pairs.empty()) return;
+    const size_t stride = 3 * (size_t)(kMutTargets + M.R);
+    HVec<MutualWork> &w = e.h_mut;
+    w.clear();
+    w.reserve(M.items);
+    for (int k = 0; k < 2; ++k) e.h_moff[k].assign((k == 0 ? M.nblk : M.nrun) + 1, 0);
+    for (auto &pr : M.pairs) {
+        const int i = pr.first, j = pr.second;
+        for (size_t a = 0; a < M.blk[i].size(); ++a) e.h_moff[0][M.blk0[i] + a + 1] += (int)M.run[j].size();
+        for (size_t b = 0; b < M.run[j].size(); ++b) e.h_moff[1][M.run0[j] + b + 1] += (int)M.blk[i].size();
+    }
+    for (int k = 0; k < 2; ++k) {
+        for (size_t q = 1; q < e.h_moff[k].size(); ++q) e.h_moff[k][q] += e.h_moff[k][q - 1];
+        e.h_ment[k].resize(M.items);
+    }
+    std::vector<int> pos[2];
+    for (int k = 0; k < 2; ++k) pos[k].assign(e.h_moff[k].begin(), e.h_moff[k].end() - 1);
+    for (auto &pr : M.pairs) {
+        const int i = pr.first, j = pr.second;
+        for (size_t a = 0; a < M.blk[i].size(); ++a)
+            for (size_t b = 0; b < M.run[j].size(); ++b) {
+                const auto &tb = M.blk[i][a], &sr = M.run[j][b];
+                const int base = (int)(w.size() * stride);  // (the scratch's size bounds it)
+                e.h_ment[0][pos[0][M.blk0[i] + a]++] = base - tb.first;
+                e.h_ment[1][pos[1][M.run0[j] + b]++] = base + 3 * kMutTargets - sr.first;
+                w.push_back(MutualWork{tb.first, tb.second, sr.first, sr.second, wt[(size_t)i * c.nd + j],
+                                       wt[(size_t)j * c.nd + i]});
+                e.mpairs += 2.0 * tb.second * sr.second;
+            }
+    }
+    e.nmut = (int)w.size();
+    auto up = [&](DBuf &d, const auto &h) {
+        d.ensure(h.size() * sizeof(h[0]));
+        HIPC(hipMemcpyAsync(d.ptr, h.data(), h.size() * sizeof(h[0]), hipMemcpyHostToDevice, c.stream));
+    };
+    up(e.mut, w);
+    for (int k = 0; k < 2; ++k) {
+        up(e.moff[k], e.h_moff[k]);
+        up(e.ment[k], e.h_ment[k]);
+    }
+    c.pair_part.ensure((size_t)M.items * stride * sizeof(double));
+}
+
 // Work lists of the pair sums for fast-summation order P (0: every pair
 // summed directly): the direct items of both grids, the nearest-region items
 // and the fast-summation plan. cb0, cb1: centres and bounding radii of the
@@ -1186,6 +1323,16 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
     std::vector<Seg> segs;
     double npairs = 0.0;
     c.n_om1 = c.n_om2 = 0;
+    // pairs of drops all in each other's region 0, neither taken by the fast
+    // summation, and with a double layer in both directions (the viscosity
+    // ratios differ from 1), in FP64
+    auto mutual = [&](int i, int j) {
+        int o;
+        return uni[(size_t)i * c.nd + j] == 0 && uni[(size_t)j * c.nd + i] == 0 && c.drops[i].lam != 1.0 &&
+               c.drops[j].lam != 1.0 && far_grid(i, j, o) < 0 && far_grid(j, i, o) < 0;
+    };
+    mutual_plan(c, mutual);
+    const bool use_mutual = !c.mut.pairs.empty();
     for (int i = 0; i < c.nd; ++i) {
         const Drop &di = c.drops[i];
         const int nti = npts(di.p);
@@ -1224,6 +1371,7 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
                 F.pair_ij.push_back(i * c.nd + j);
                 continue;
             }
+            if (use_mutual && mutual(i, j)) continue;
             const int8_t ru = uni[(size_t)i * c.nd + j];
             if (ru == 0 || ru == 1) {
                 // every target of i in one region: items over the contiguous
@@ -1376,7 +1524,10 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     c.pair_ch = 0;
     pair_shape(c, c.npairs_direct, rT, rch);
     std::vector<std::pair<int, int>> cand;
-    for (int T : {4, 2, 1}) {
+    // one target per lane only where the rule takes it: timed by itself it wins by
+    // 3 to 5 % at some shapes, but an operator application it was chosen for ran
+    // 6 % slower beside other work (three drops of degree 37: 161 -> 171 us)
+    for (int T : {4, 2}) {
         int T0 = T, ch0 = 64;
         c.pair_T_fix = T;
         c.pair_ch = 0;
@@ -1538,6 +1689,7 @@ static Ctx::WList &work_lists(Ctx &c, const std::vector<double> &wt)
         HIPC(hipMemcpyAsync(e->d.ptr, keep.data(), keep.size() * sizeof(PairWork), hipMemcpyHostToDevice, c.stream));
     e->n = (int)keep.size();
     gather_lists(c, keep, c.tlist_h, c.T, true, 64 * c.pair_T, e->g);
+    mutual_list(c, wt, *e);
     if (!c.near_h.empty()) {
         HVec<double> &nw = e->h_nw;
         nw.resize(c.near_h.size());
@@ -1633,6 +1785,18 @@ static void run_pairs(Ctx &c, int kind, const std::vector<double> &wt)
             launch_pair_gather(c.stream, (int)c.T, tile, c.tile_of.as<int>(), L.g.toff.as<int>(), L.g.tent.as<int>(),
                                L.g.off.as<int>(), L.g.ent.as<int>(), part, c.acc.d(), c.T, true);
         }
+    }
+    if (L.nmut > 0) {  // its partial sums reuse the buffer, in stream order
+        double *part = c.part_override ? c.part_override : c.pair_part.d();
+        {
+            ProfScope ps(c, kind == 0 ? "pair_sl" : "pair_dl", L.mpairs * fpp, 0.0);
+            launch_mutual(c.stream, kind, L.nmut, L.mut.as<MutualWork>(), c.mut.R, g0, part);
+        }
+        ProfScope ps(c, "pair_gather", 0.0, 8.0 * 3.0 * (double)L.nmut * (kMutTargets + c.mut.R));
+        launch_mutual_gather(c.stream, (int)c.T,
+                             MutualGather{c.mut.dtb.as<int>(), L.moff[0].as<int>(), L.ment[0].as<int>(),
+                                          c.mut.dsr.as<int>(), L.moff[1].as<int>(), L.ment[1].as<int>(), c.mut.R},
+                             part, c.acc.d(), c.T);
     }
     run_fmm(c, kind, L);
 }
@@ -2687,7 +2851,6 @@ int bim_default_options(bim_options *o)
 // until the process ends; its device address is looked up once per device
 // (in bim_create, with the device current) and kept in g_scratch.
 // --------------------------------------------------------------------------
-constexpr size_t kScratchDoubles = (size_t)1 << 25;  // 256 MiB
 static __device__ __align__(256) double scratch[kScratchDoubles];
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;

@@ -57,6 +57,23 @@ struct PairWork {
 constexpr int kPairContig = 2;
 constexpr int kPairSmall = 4;
 
+// Mutual drop pairs (kernels_mutual.hip): targets [t0, t0 + nt) of one drop
+// against the sources [s0, s0 + ns) of another, both ways (standard-grid
+// nodes); weights of the targets' and of the sources' sums.
+struct MutualWork {
+    int t0, nt, s0, ns;
+    double wt, ws;
+};
+constexpr int kMutTargets = 1024;  // targets per item, at most
+
+// Slots of the items of mutual pairs (k_mutual_gather): target t's cells are
+// the block tb[t] of targets and the run sr[t] of sources it lies in, each with
+// a list of slot bases (CSR); component strides kMutTargets and R.
+struct MutualGather {
+    const int *tb, *toff, *tent, *sr, *soff, *sent;
+    int R;
+};
+
 // Device state of the GMRES least-squares problem (Givens rotations applied
 // on the device): R by columns, rotations, right-hand side g, and the
 // residual estimate |g[k+1]| / ||b|| of the latest column.

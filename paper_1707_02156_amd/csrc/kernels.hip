@@ -511,8 +511,9 @@ __device__ inline void pair64(double X, double Y, double Z, double px, double py
     // of the sums (1e-10 and below) by the first-order correction of the
     // power the kernel needs: with e = r2 y^2 - 1 = 2 d + d^2,
     //   r^-1 = y (1 + e)^(-1/2) ~ y (1 - e/2)          (SL; one Newton step),
-    //   r^-5 = y^5 (1 + e)^(-5/2) ~ y^5 (1 - 5 e / 2)  (DL),
-    // leaving relative errors of 3/8 e^2 and 35/8 e^2 (below 5e-14): 4 and 6
+    //   r^-5 = y^5 (1 + e)^(-5/2) ~ y^5 (1 - 5 e / 2) = -5/2 y^5 (r2 y^2 - 7/5)  (DL;
+    //          the factor -5/2 is in the item's weight),
+    // leaving relative errors of 3/8 e^2 and 35/8 e^2 (below 5e-14): 4 and 5
     // FP64 instructions on top of the estimate.
     const double y = __builtin_amdgcn_rsq(r2);
     const double hd = fma(hz, u2, fma(hy, u1, hx * u0));
@@ -526,9 +527,7 @@ __device__ inline void pair64(double X, double Y, double Z, double px, double py
     } else {
         const double hn = fma(hz, m2, fma(hy, m1, hx * m0));
         const double z = y * y;
-        const double e = fma(r2, z, -1.0);
-        const double y5 = z * z * y;
-        const double sc = (hd * hn) * fma(y5 * -2.5, e, y5);
+        const double sc = (hd * hn) * ((z * z) * (y * fma(r2, z, -1.4)));  // times -0.4 of r^-5
         A0 = fma(sc, hx, A0);
         A1 = fma(sc, hy, A1);
         A2 = fma(sc, hz, A2);
@@ -590,7 +589,7 @@ __device__ inline void pair_item64(const PairWork &w, int item, int tile, const 
             for (int v = 0; v < U; ++v) step(s + v, v);
         for (; s < w.nsrc; ++s) step(s, 0);
     }
-    const double sw = KIND == 0 ? w.w : -6.0 * w.w;
+    const double sw = KIND == 0 ? w.w : 15.0 * w.w;
     double *out = part + (long)item * (3 * tile) + lane;
 #pragma unroll
     for (int k = 0; k < T; ++k) {
