@@ -101,7 +101,8 @@ __global__ void k_force(int npt, const double *__restrict__ syn, int eos, double
     if (eos == 0) { sig = sigma0; ds = 0.0; }
     else if (eos == 1) { sig = 1.0 - E * xs * F(18); ds = -E * xs; }
     else { const double g = 1.0 - xs * F(18); sig = 1.0 + E * log(g); ds = -E * xs / g; }
-    const double st = ds * F(19), sp = ds * F(20);
+    // the surfactant's fields are there only with an equation of state that reads it
+    const double st = eos == 0 ? 0.0 : ds * F(19), sp = eos == 0 ? 0.0 : ds * F(20);
     const double cpn = (Gm * sp - Fm * st) / W2, ctn = (Em * st - Fm * sp) / W2;
     for (int c = 0; c < 3; ++c) f[(long)c * npt + i] = 2.0 * sig * K * n[c] - (cpn * ap[c] + ctn * at[c]);
 }
