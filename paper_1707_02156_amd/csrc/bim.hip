@@ -135,6 +135,9 @@ void launch_gs_update_dots(hipStream_t st, long n, int kv, const double *V, long
 void launch_gs_update_norm(hipStream_t st, long n, int kv, const double *V, long ld, const double *h2, double *w,
                            double *part, unsigned *cnt, double *h, const GivensArgs &ga = GivensArgs{},
                            double *vout = nullptr);
+bool gs_small(long n, int kv);
+void launch_gs_small(hipStream_t st, long n, int kv, const double *V, const double *w, const GivensArgs &ga,
+                     double *vout);
 void launch_backsub(hipStream_t st, int k, const double *H, long ldH, const double *g, double *y);
 void launch_gs_scale(hipStream_t st, long n, const double *w, const double *nrm, double *v);
 void launch_surf_terms(hipStream_t st, const SurfJob *jobs, int n);
@@ -2675,6 +2678,10 @@ static int gmres_op(Ctx &c, long n, const OpFn &apply, const double *b, double *
             GivensArgs gk = ga;
             gk.res = resdev + 2 * (k & 1);  // written by the device into pinned host memory
             gk.stamp = stamp[k & 1] = (c.gm_seq += 1.0);
+            if (gs_small(n, k + 1)) {
+                launch_gs_small(c.stream, n, k + 1, V, w, gk, V + (long)(k + 1) * n);
+                return;
+            }
             launch_gs_dots(c.stream, n, k + 1, V, n, w, part, cnt, h);
             launch_gs_update_dots(c.stream, n, k + 1, V, n, h, w, part, cnt, h2);
             launch_gs_update_norm(c.stream, n, k + 1, V, n, h2, w, part, cnt, h, gk, V + (long)(k + 1) * n);

@@ -853,6 +853,33 @@ constexpr int kGsR = 4, kGsChunk = 64 * kGsR;
 constexpr int kGsMaxVectors = 256;  // Krylov vectors; the Givens staging below needs 3 (kv - 1) + 2 doubles of sacc
 static_assert(3 * (kGsMaxVectors - 1) + 2 <= 4 * kGsChunk, "Givens staging exceeds the LDS buffer");
 
+// Givens update for column kc of H (one thread): the previous rotations scs,
+// ssn on its entries scol[0..kc + 1], then the rotation that zeroes the last; g
+// (g[kc] given) updated and the residual estimate |g[kc+1]| / ||b|| stored.
+__device__ inline void givens_column(int kc, double *scol, const double *scs, const double *ssn, double gk,
+                                     const GivensArgs &ga)
+{
+    double cur = scol[0];  // entry l of the column after rotations 0..l-1
+    for (int l = 0; l < kc; ++l) {
+        const double nx = scol[l + 1];
+        scol[l] = scs[l] * cur + ssn[l] * nx;
+        cur = -ssn[l] * cur + scs[l] * nx;
+    }
+    const double hk1 = scol[kc + 1];
+    const double den = hypot(cur, hk1);
+    const double cr = den > 0.0 ? cur / den : 1.0, sr = den > 0.0 ? hk1 / den : 0.0;
+    ga.cs[kc] = cr;
+    ga.sn[kc] = sr;
+    scol[kc] = den;
+    scol[kc + 1] = 0.0;
+    ga.g[kc + 1] = -sr * gk;
+    ga.g[kc] = cr * gk;
+    ga.res[0] = fabs(ga.g[kc + 1]) / ga.bnorm;  // host-visible memory
+    __threadfence_system();
+    ga.res[1] = ga.stamp;  // the host reads the estimate once it sees this step's stamp
+    __threadfence_system();
+}
+
 template <bool UPD, bool NRM>
 __global__ __launch_bounds__(256) void k_gs(long n, int kv, const double *__restrict__ V, long ld,
                                             const double *__restrict__ hin, double *__restrict__ w,
@@ -985,32 +1012,116 @@ __global__ __launch_bounds__(256) void k_gs(long n, int kv, const double *__rest
             sgk = ga.g[kc];
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            double cur = scol[0];  // entry l of the column after rotations 0..l-1
-            for (int l = 0; l < kc; ++l) {
-                const double nx = scol[l + 1];
-                scol[l] = scs[l] * cur + ssn[l] * nx;
-                cur = -ssn[l] * cur + scs[l] * nx;
-            }
-            const double hk1 = scol[kc + 1];
-            const double den = hypot(cur, hk1);
-            const double cr = den > 0.0 ? cur / den : 1.0, sr = den > 0.0 ? hk1 / den : 0.0;
-            ga.cs[kc] = cr;
-            ga.sn[kc] = sr;
-            scol[kc] = den;
-            scol[kc + 1] = 0.0;
-            ga.g[kc + 1] = -sr * sgk;
-            ga.g[kc] = cr * sgk;
-            ga.res[0] = fabs(ga.g[kc + 1]) / ga.bnorm;  // host-visible memory
-            __threadfence_system();
-            ga.res[1] = ga.stamp;  // the host reads the estimate once it sees this step's stamp
-            __threadfence_system();
-        }
+        if (threadIdx.x == 0) givens_column(kc, scol, scs, ssn, sgk, ga);
         __syncthreads();
         double *col = ga.H + (long)kc * ga.ldH;  // column kc of R, rows 0..kc+1
         for (int l = threadIdx.x; l <= kc + 1; l += 256) col[l] = scol[l];
     }
     if (threadIdx.x == 0) atomicExch(cnt, 0u);
+}
+
+// The whole orthogonalisation of an Arnoldi step (both passes, the norm, the
+// new basis vector and the Givens update) by one block, for small systems: w
+// stays in LDS, the block's barriers take the place of two launches and of the
+// last block's ticket in each of three. Bound: the L2 rate of one CU (the
+// basis is read four times), so the three-kernel form takes over where n kv is
+// large (gs_small). Sums in a fixed order: a basis vector's product is split
+// over S wavefronts (a power of two), added in order.
+// Measured per step: n = 1836, kv 1..15: 12 us against 23 for the three
+// kernels; n = 6732: 12 us at kv = 1, 36 at kv = 17, against 26 and 33.
+constexpr int kGsSmallThreads = 1024, kGsSmallWaves = kGsSmallThreads / 64;
+
+__global__ __launch_bounds__(kGsSmallThreads) void k_gs_small(int n2, int kv, const double2 *__restrict__ V, long ld2,
+                                                              const double2 *__restrict__ w, GivensArgs ga,
+                                                              double2 *__restrict__ vout)
+{
+    extern __shared__ double2 sw[];  // w
+    __shared__ double spart[kGsMaxVectors], sh[kGsMaxVectors], scol[kGsMaxVectors + 2], scs[kGsMaxVectors],
+        ssn[kGsMaxVectors], snrm[kGsSmallWaves], sgk;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), kc = kv - 1;
+    for (int e = tid; e < n2; e += kGsSmallThreads) sw[e] = w[e];
+    if (tid < kc) {
+        scs[tid] = ga.cs[tid];
+        ssn[tid] = ga.sn[tid];
+    }
+    if (tid == 0) sgk = ga.g[kc];
+    int S = kGsSmallWaves;
+    while (S > 1 && S * kv > kGsSmallWaves) S >>= 1;
+    const int seg = (n2 + S - 1) / S;
+    double q = 0.0;  // this thread's part of ||w||^2
+    for (int pass = 0; pass < 2; ++pass) {
+        __syncthreads();
+        for (int task = wv; task < kv * S; task += kGsSmallWaves) {
+            const int i = task / S, e0 = task % S * seg, e1 = min(n2, e0 + seg);
+            const double2 *Vi = V + i * ld2;
+            double s0 = 0.0, s1 = 0.0;
+            int e = e0 + lane;
+            for (; e + 7 * 64 < e1; e += 8 * 64) {
+                double2 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = Vi[e + 64 * u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const double2 x = sw[e + 64 * u];
+                    s0 = fma(v[u].x, x.x, s0);
+                    s1 = fma(v[u].y, x.y, s1);
+                }
+            }
+            for (; e < e1; e += 64) {
+                const double2 v = Vi[e], x = sw[e];
+                s0 = fma(v.x, x.x, s0);
+                s1 = fma(v.y, x.y, s1);
+            }
+            s0 += s1;
+            for (int o = 32; o > 0; o >>= 1) s0 += __shfl_down(s0, o, 64);
+            if (lane == 0) spart[task] = s0;
+        }
+        __syncthreads();
+        if (tid < kv) {
+            double s = spart[tid * S];
+            for (int k = 1; k < S; ++k) s += spart[tid * S + k];
+            sh[tid] = s;
+            scol[tid] = pass ? scol[tid] + s : s;
+        }
+        __syncthreads();
+        for (int e = tid; e < n2; e += kGsSmallThreads) {
+            double2 a = make_double2(0.0, 0.0);
+            int i = 0;
+            for (; i + 8 <= kv; i += 8) {
+                double2 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = V[(i + u) * ld2 + e];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    a.x = fma(sh[i + u], v[u].x, a.x);
+                    a.y = fma(sh[i + u], v[u].y, a.y);
+                }
+            }
+#pragma unroll 4
+            for (; i < kv; ++i) {
+                const double2 v = V[i * ld2 + e];
+                a.x = fma(sh[i], v.x, a.x);
+                a.y = fma(sh[i], v.y, a.y);
+            }
+            const double2 x = make_double2(sw[e].x - a.x, sw[e].y - a.y);
+            sw[e] = x;
+            if (pass) q = fma(x.x, x.x, fma(x.y, x.y, q));
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) q += __shfl_down(q, o, 64);
+    if (lane == 0) snrm[wv] = q;
+    __syncthreads();
+    double s = 0.0;
+    for (int k = 0; k < kGsSmallWaves; ++k) s += snrm[k];
+    const double t = sqrt(s), ti = t > 0.0 ? 1.0 / t : 0.0;  // zero norm: v = 0
+    for (int e = tid; e < n2; e += kGsSmallThreads) vout[e] = make_double2(sw[e].x * ti, sw[e].y * ti);
+    if (tid == 0) {
+        scol[kv] = t;
+        givens_column(kc, scol, scs, ssn, sgk, ga);
+    }
+    __syncthreads();
+    double *col = ga.H + (long)kc * ga.ldH;  // column kc of R, rows 0..kc+1
+    if (tid <= kc + 1) col[tid] = scol[tid];
 }
 
 // y = R^-1 g for the leading k x k block of the upper triangular R stored by
@@ -1271,6 +1382,23 @@ void launch_gs_update_norm(hipStream_t st, long n, int kv, const double *V, long
         hipLaunchKernelGGL((k_gs<false, true>), dim3(nb), dim3(256), 0, st, n, 0, V, ld, nullptr, w, part, cnt, h,
                            GivensArgs{}, vk);
     if (vout && !vk) hipLaunchKernelGGL(k_gs_scale, dim3(nblk(n)), dim3(256), 0, st, n, w, h + kv, vout);
+}
+
+// Whether the one-block form takes an Arnoldi step: w fits 64 KB of LDS, and
+// reading the basis at one CU's L2 rate (1.5 us per vector at n = 6732) costs
+// less than the two launches it saves: up to twelve vectors there.
+bool gs_small(long n, int kv)
+{
+    return n % 2 == 0 && n <= 8192 && kv <= kGsMaxVectors && n * kv <= 81920;
+}
+
+// Arnoldi step k = kv - 1: w orthogonalised against V_0..V_k, vout = w / ||w||,
+// Givens update (w itself is left as it is).
+void launch_gs_small(hipStream_t st, long n, int kv, const double *V, const double *w, const GivensArgs &ga,
+                     double *vout)
+{
+    hipLaunchKernelGGL(k_gs_small, dim3(1), dim3(kGsSmallThreads), n * sizeof(double), st, (int)(n / 2), kv,
+                       (const double2 *)V, n / 2, (const double2 *)w, ga, (double2 *)vout);
 }
 
 void launch_backsub(hipStream_t st, int k, const double *H, long ldH, const double *g, double *y)
