@@ -533,7 +533,7 @@ __global__ __launch_bounds__(64 * kFkMaxWaves) __attribute__((amdgpu_waves_per_e
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const double ok = (q < 2 ? one : two) ? 1.0 : 0.0;
+                    const bool ok = q < 2 ? one : two;
                     double(&h)[3][4] = x[u];
                     const double n0 = xt[u][1][q] * N[u][2][q] - xt[u][2][q] * N[u][1][q];
                     const double n1 = xt[u][2][q] * N[u][0][q] - xt[u][0][q] * N[u][2][q];
@@ -544,11 +544,13 @@ __global__ __launch_bounds__(64 * kFkMaxWaves) __attribute__((amdgpu_waves_per_e
                     for (int c = 0; c < 3; ++c) h[c][q] *= ri;
                     if (SL) {
                         const double nn = n0 * n0 + n1 * n1 + n2 * n2;
-                        Wr[u][q] = ok * om * (nn * rsq_full(nn)) * ri;
+                        const double W = om * (nn * rsq_full(nn)) * ri;
+                        Wr[u][q] = ok ? W : 0.0;
                     }
                     if (DL) {
                         const double hn = h[0][q] * n0 + h[1][q] * n1 + h[2][q] * n2;
-                        sc[u][q] = ok * -6.0 * om * hn * (ri * ri);
+                        const double sv = -6.0 * om * hn * (ri * ri);
+                        sc[u][q] = ok ? sv : 0.0;
                     }
                     // formed here, not after the sums of f, so that x_theta and
                     // x_phi are not held over them
