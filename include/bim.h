@@ -117,8 +117,8 @@ typedef struct {
                             and centres of i's nodes and of j's source grid); the others are
                             summed directly */
     double fmm_eps;      /* truncation bound of a far pair, in (0, 1) */
-    int pair_tune;       /* 1: the work-item shape of the direct pair sums (targets per lane 1, 2
-                            or 4; sources per item) is chosen by timing a double-layer pair pass
+    int pair_tune;       /* 1: the work-item shape of the direct pair sums (targets per lane,
+                            sources per item) is chosen by timing a double-layer pair pass
                             of each candidate at the first evaluation after bim_set_drops, and
                             kept for later contexts of the same problem shape (same number of
                             pairs to two digits, targets, fast-summation order) in the process;
@@ -329,8 +329,7 @@ int bim_sh_analyze(bim_ctx ctx, int q, int p, int nf, const double *grid, double
 int bim_synchronize(bim_ctx ctx);
 
 /* Kernel timing: HIP events recorded around each launch of the main kernels,
- * on the stream the launch goes to (the context stream; the singular pipeline
- * of a velocity evaluation runs on a second stream of the context). enable = 1 clears the totals and starts recording,
+ * on the context's stream. enable = 1 clears the totals and starts recording,
  * 0 stops. Kernel names: "pipe_rotate", "pipe_legendre", "pipe_fourier",
  * "pipe_adjrot" (batched singular pipeline), "sing_fused" (fused singular
  * rule), "sing_rotate" and "sing_v1" (per-application singular path),

@@ -125,7 +125,6 @@ void launch_dl_apply(hipStream_t st, int nt, int nc2, const double *M, const dou
 void launch_rhs(hipStream_t st, int T, const double *tx, long tstride, const double *s, double a, const double *U0,
                 const double *gU_dev, double *b);
 void launch_scale_add(hipStream_t st, long n, double a, const double *x, double b, double *y);
-void launch_op_combine(hipStream_t st, long n, const double *sc, const double *x, double *y);
 long gs_blocks(long n);
 int gs_max_vectors();
 void launch_gs_dots(hipStream_t st, long n, int kv, const double *V, long ld, double *w, double *part,
@@ -195,15 +194,24 @@ static thread_local bool t_no_alloc = false;
 struct DBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
+    bool own = true;  // false: a part of another buffer
     DBuf() = default;
     DBuf(const DBuf &) = delete;
     DBuf &operator=(const DBuf &) = delete;
     ~DBuf() { release(); }
     void release()
     {
-        if (ptr) (void)hipFree(ptr);
+        if (ptr && own) (void)hipFree(ptr);
         ptr = nullptr;
         bytes = 0;
+        own = true;
+    }
+    void part_of(void *p, size_t b)
+    {
+        release();
+        ptr = p;
+        bytes = b;
+        own = false;
     }
     void ensure(size_t b)
     {
@@ -211,7 +219,7 @@ struct DBuf {
         if (t_no_alloc)
             throw Error{BIM_ESTATE, "the call would allocate device memory (" + std::to_string(b) +
                                         " bytes): apply bim_apply_double_layer once to these drops first"};
-        const bool regrow = ptr != nullptr;
+        const bool regrow = ptr != nullptr && own;
         release();
         if (b == 0) b = 8;
         // grow with slack: freeing device memory waits for the whole device,
@@ -219,6 +227,12 @@ struct DBuf {
         if (regrow) b += b / 4;
         HIPC(hipMalloc(&ptr, b));
         bytes = b;
+    }
+    void swap(DBuf &o)
+    {
+        std::swap(ptr, o.ptr);
+        std::swap(bytes, o.bytes);
+        std::swap(own, o.own);
     }
     double *d() const { return static_cast<double *>(ptr); }
     template <class T> T *as() const { return static_cast<T *>(ptr); }
@@ -271,13 +285,8 @@ struct Ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    // second stream: the singular pipeline of the single-layer pass runs on
-    // it while the context's stream classifies the regions and the host
-    // builds the pair lists; the context's stream waits for ev_join before
-    // the pipeline's results are used
-    hipStream_t side = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    bool join_pending = false;
+    hipEvent_t ev_reg = nullptr;  // the regions' readback (regions_begin)
+    bool reg_pending = false;     // it is enqueued and not yet read
     std::string err;
 
     int nd = 0;
@@ -294,20 +303,29 @@ struct Ctx {
     DBuf xc, gc, fc, gU;
     DBuf tx, s0N, s0W, s0d;        // standard-grid nodes [3][T]
     DBuf s1x, s1N, s1W, s1d;       // upsampled nodes [3][S1]
-    DBuf tdrop, vol, hj, noff, ncnt, hfac, hbad;
+    DBuf tdrop, vol, hj, noff, ncnt, hfac;
     DBuf volpart, voloff;  // per-wavefront partial volumes of the standard grids, and each drop's first
     std::vector<int> voloff_h;
+    // tables that hang on the degrees alone (the buffers above and below that are
+    // parts of tab), one upload for a new list of degrees tab_p
+    DBuf tab;
+    HVec<char> h_tab;
+    std::vector<int> tab_p;
+    std::vector<int> sys_up;  // the systems in sysd
+    bool upload_pending = false;  // an upload from the pinned images may still run
     DBuf unoff, uncnt, cbnd1;  // upsampled grids: node offsets, counts, centres and radii
     std::vector<int> sys_h;  // independent system of each drop (bim_set_systems)
     DBuf sysd;
     DBuf reg, dist, cbnd, clist, ccount;
     bool regions_exact = false;  // distances of every pair computed (bim_regions with dist)
     DBuf tlist;
-    std::vector<int> tlist_h;         // host image of tlist
+    HVec<int> tlist_h;                // host image of tlist
+    bool lists_pending = false;       // its upload may still run
     std::vector<PairWork> w0h, w1h;   // pair work templates (weights per pass)
     int pair_ch = 0;                  // sources per pair work item (0: from the pair count)
     int pair_T_fix = 0;               // targets per lane of whole tiles (0: from the pair count)
     int pair_T = 4;                   // targets per lane of the whole-tile pair items in use
+    int last_T = 0, last_ch = 0;      // the shape chosen by timing last (0: none yet)
     bool pair_tuned = false;          // pair_T_fix / pair_ch chosen by tune_pairs for these drops
     double npairs_direct = 0.0;       // direct pairs of one application (the last build_lists)
     DBuf pair_part;                   // partial sums of the pair work items [item][3][64 pair_T]
@@ -362,7 +380,8 @@ struct Ctx {
         DBuf fp;             // far pairs of the fast summation with their weights
     };
     std::vector<std::unique_ptr<WList>> wlists;
-    std::vector<int8_t> reg_h;
+    HVec<int8_t> reg_h;  // the regions and, 8-aligned after them, the volume check
+    HVec<double> cb_h;   // bounding spheres of the standard and the upsampled grids [2][nd][4]
     int n_om1 = 0, n_om2 = 0;
     // fast summation of far drop pairs (opt.fmm_order != 0): multipole slots
     // (drop, source grid), target slots (drops), pairs grouped by target slot
@@ -403,17 +422,15 @@ struct Ctx {
     int near_nwork = 0;
     long near_ldp = 0;
     double near_pairs = 0.0;
-    DBuf acc, tmp, bvec, scl;      // [3][T] accumulators, [3][Ctot] vectors
-    DBuf acc2;                     // [3][T] the single-layer pipeline's part when it runs on the second stream
+    DBuf acc, tmp, bvec;           // [3][T] accumulators, [3][Ctot] vectors
+    DBuf acc2;                     // [3][T] accumulator of passes that are only timed
     DBuf synbuf, Gbuf, Rbuf, Fbuf, fgrid;
     // per drop: stored singular double-layer rows. The buffers are kept
     // (grown, never freed) when new drops are set: freeing device memory
     // waits for the whole device and a fresh large allocation is slow, which
     // a server slot would pay at every request
     std::vector<std::unique_ptr<DBuf>> Mdl;
-    // pinned host images of the per-drop tables set_drops uploads
-    HVec<int> h_tdrop, h_noff, h_ncnt, h_unoff, h_uncnt, h_sys;
-    HVec<double> h_xc, h_hfac, h_scl, h_gU;
+    HVec<double> h_xc;  // pinned host image of the drop coefficients
     std::vector<char> Mok;
     DBuf V, hbuf, ybuf, wvec, xsol, rvec, gspart, gscnt, givbuf;
     DBuf bcorr, xcorr;  // per-system corrections of a joint solve
@@ -477,12 +494,7 @@ struct Ctx {
         rots.clear();
         if (hhost) (void)hipHostFree(hhost);
         if (hres) (void)hipHostFree(hres);
-        if (side) {
-            (void)hipStreamSynchronize(side);
-            (void)hipStreamDestroy(side);
-        }
-        if (ev_fork) (void)hipEventDestroy(ev_fork);
-        if (ev_join) (void)hipEventDestroy(ev_join);
+        if (ev_reg) (void)hipEventDestroy(ev_reg);
         if (own_stream && stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -508,9 +520,7 @@ struct ProfScope {
     Ctx &c;
     Ctx::ProfEntry *e = nullptr;
     hipEvent_t a = nullptr;
-    hipStream_t st;
-    ProfScope(Ctx &cc, const char *name, double flops, double bytes, hipStream_t s = nullptr)
-        : c(cc), st(s ? s : cc.stream)
+    ProfScope(Ctx &cc, const char *name, double flops, double bytes) : c(cc)
     {
         if (!c.prof_on) return;
         Ctx::ProfEntry *pe = &c.prof[name];
@@ -520,20 +530,19 @@ struct ProfScope {
         if (!c.prof_sel.empty() && !c.prof_sel.count(name)) return;
         e = pe;
         a = prof_event(c);
-        HIPC(hipEventRecord(a, st));
+        HIPC(hipEventRecord(a, c.stream));
     }
     ~ProfScope()
     {
         if (!e) return;
         hipEvent_t b = prof_event(c);
-        if (hipEventRecord(b, st) == hipSuccess) e->pend.emplace_back(a, b);
+        if (hipEventRecord(b, c.stream) == hipSuccess) e->pend.emplace_back(a, b);
     }
 };
 
 static void prof_drain(Ctx &c)
 {
     HIPC(hipStreamSynchronize(c.stream));
-    if (c.side) HIPC(hipStreamSynchronize(c.side));
     for (auto &kv : c.prof) {
         for (auto &pr : kv.second.pend) {
             float ms = 0.0f;
@@ -778,11 +787,7 @@ static void build_nodes(Ctx &c)
     syn_layout(c, o0, o1, og, tot);
     c.synbuf.ensure((size_t)tot * sizeof(double));
     c.vol.ensure(c.nd * sizeof(double));
-    c.voloff_h.assign(c.nd + 1, 0);
-    for (int i = 0; i < c.nd; ++i) c.voloff_h[i + 1] = c.voloff_h[i] + (npts(c.drops[i].p) + 63) / 64;
     c.volpart.ensure((size_t)c.voloff_h[c.nd] * sizeof(double));
-    c.voloff.ensure((size_t)(c.nd + 1) * sizeof(int));
-    HIPC(hipMemcpyAsync(c.voloff.ptr, c.voloff_h.data(), (c.nd + 1) * sizeof(int), hipMemcpyHostToDevice, c.stream));
     std::vector<SynJob> jobs;
     for (int i = 0; i < c.nd; ++i) {
         const Drop &d = c.drops[i];
@@ -868,6 +873,15 @@ static NearArgs near_args(Ctx &c)
     return a;
 }
 
+// Whether two drops of one system interact (there are pair sums).
+static bool drop_pairs(const Ctx &c)
+{
+    for (int i = 0; i < c.nd; ++i)
+        for (int j = i + 1; j < c.nd; ++j)
+            if (c.sys_h[i] == c.sys_h[j]) return true;
+    return false;
+}
+
 // Work-item shape of the pair sums from the pairs of one application:
 // targets per lane T of the whole tiles (2; 1 when even the shortest source
 // runs would leave fewer than kPairItemsMin items, as for two drops of
@@ -927,8 +941,8 @@ static void pair_items(std::vector<PairWork> &w, int tl_off, int cnt, bool conti
 // contiguous tile k adds its base slot minus the tile's first target to tile
 // k's list; an item over an index list adds the slot of each of its targets
 // to that target's list. Both in item order.
-template <class Items>
-static void gather_lists(Ctx &c, const Items &items, const std::vector<int> &tl, long nt, bool tiles, int tile,
+template <class Items, class List>
+static void gather_lists(Ctx &c, const Items &items, const List &tl, long nt, bool tiles, int tile,
                          Ctx::Gather &g)
 {
     REQUIRE((double)items.size() * 3 * tile < 2147483647.0, BIM_ENOMEM, "too many pair work items");
@@ -975,7 +989,7 @@ static void gather_lists(Ctx &c, const Items &items, const std::vector<int> &tl,
 // splits a contiguous target set.
 static void target_tiles(Ctx &c, int T)
 {
-    c.tile_of_h.resize(std::max<long>(1, c.T));
+    std::vector<int> tile_of(std::max<long>(1, c.T));
     c.tile_start_h.clear();
     for (const Drop &d : c.drops) {
         const int nt = npts(d.p);
@@ -983,10 +997,12 @@ static void target_tiles(Ctx &c, int T)
             bool whole = true;
             const int sz = pair_chunk(T, nt - a, whole);
             c.tile_start_h.push_back((int)(d.toff + a));
-            for (int b = a; b < a + sz; ++b) c.tile_of_h[d.toff + b] = (int)c.tile_start_h.size() - 1;
+            for (int b = a; b < a + sz; ++b) tile_of[d.toff + b] = (int)c.tile_start_h.size() - 1;
             a += sz;
         }
     }
+    if (tile_of == c.tile_of_h) return;  // the same degrees and tiles as before
+    c.tile_of_h = std::move(tile_of);
     c.tile_of.ensure(c.tile_of_h.size() * sizeof(int));
     HIPC(hipMemcpyAsync(c.tile_of.ptr, c.tile_of_h.data(), c.tile_of_h.size() * sizeof(int), hipMemcpyHostToDevice,
                         c.stream));
@@ -1003,27 +1019,10 @@ static void near_setup(Ctx &c)
     const int L = c.opt.near_L;
     const long V = (long)n * L;
     int pmax = 0;
-    std::vector<int> dp(c.nd), dtoff(c.nd), gloff(c.nd);
-    std::vector<long> dcoff(c.nd);
-    std::vector<double> glt;
-    for (int i = 0; i < c.nd; ++i) {
-        const Drop &d = c.drops[i];
-        dp[i] = d.p;
-        dtoff[i] = (int)d.toff;
-        dcoff[i] = d.coff;
-        gloff[i] = (int)glt.size();
-        GridTab &g = grid(c, d.p, d.p);
-        glt.insert(glt.end(), g.t.begin(), g.t.end());
-        pmax = std::max(pmax, d.p);
-    }
+    for (const Drop &d : c.drops) pmax = std::max(pmax, d.p);
     REQUIRE(pmax <= 63, BIM_EINVAL, "the nearest-region rule supports degrees up to 63");
     c.near_ldp = ncoef(pmax);
     c.near_items.ensure(n * sizeof(NearItem));
-    c.near_dp.ensure(c.nd * sizeof(int));
-    c.near_dtoff.ensure(c.nd * sizeof(int));
-    c.near_gloff.ensure(c.nd * sizeof(int));
-    c.near_dcoff.ensure(c.nd * sizeof(long));
-    c.near_glt.ensure(glt.size() * sizeof(double));
     c.near_par.ensure((size_t)n * 4 * sizeof(double));
     c.near_vx.ensure((size_t)3 * V * sizeof(double));
     c.near_vreg.ensure((size_t)V);
@@ -1032,11 +1031,6 @@ static void near_setup(Ctx &c)
     c.near_self.ensure((size_t)3 * c.T * sizeof(double));
     c.near_selfc.ensure((size_t)3 * c.Ctot * sizeof(double));
     HIPC(hipMemcpyAsync(c.near_items.ptr, c.near_h.data(), n * sizeof(NearItem), hipMemcpyHostToDevice, c.stream));
-    HIPC(hipMemcpyAsync(c.near_dp.ptr, dp.data(), c.nd * sizeof(int), hipMemcpyHostToDevice, c.stream));
-    HIPC(hipMemcpyAsync(c.near_dtoff.ptr, dtoff.data(), c.nd * sizeof(int), hipMemcpyHostToDevice, c.stream));
-    HIPC(hipMemcpyAsync(c.near_gloff.ptr, gloff.data(), c.nd * sizeof(int), hipMemcpyHostToDevice, c.stream));
-    HIPC(hipMemcpyAsync(c.near_dcoff.ptr, dcoff.data(), c.nd * sizeof(long), hipMemcpyHostToDevice, c.stream));
-    HIPC(hipMemcpyAsync(c.near_glt.ptr, glt.data(), glt.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
     launch_near_setup(c.stream, near_args(c));
     std::vector<int8_t> vreg(V);
     HIPC(hipMemcpyAsync(vreg.data(), c.near_vreg.ptr, V, hipMemcpyDeviceToHost, c.stream));
@@ -1189,8 +1183,7 @@ template <class F> static void mutual_plan(Ctx &c, F &&mutual)
     M.run.assign(c.nd, {});
     M.blk0.assign(c.nd, 0);
     M.run0.assign(c.nd, 0);
-    M.tb.resize(c.T);
-    M.sr.resize(c.T);
+    std::vector<int> tb(c.T), sr(c.T);
     M.nblk = M.nrun = 0;
     for (int i = 0; i < c.nd; ++i) {
         const int n = npts(c.drops[i].p), t0 = (int)c.drops[i].toff;
@@ -1203,17 +1196,19 @@ template <class F> static void mutual_plan(Ctx &c, F &&mutual)
         };
         M.blk0[i] = M.nblk;
         M.run0[i] = M.nrun;
-        split(blocks(i), 64, M.blk[i], M.tb, M.nblk);
-        split((n + M.R - 1) / M.R, 16, M.run[i], M.sr, M.nrun);
+        split(blocks(i), 64, M.blk[i], tb, M.nblk);
+        split((n + M.R - 1) / M.R, 16, M.run[i], sr, M.nrun);
     }
     M.items = 0;
     for (auto &pr : M.pairs) M.items += (long)M.blk[pr.first].size() * M.run[pr.second].size();
-    auto up = [&](DBuf &d, const std::vector<int> &h) {
+    auto up = [&](DBuf &d, std::vector<int> &h, std::vector<int> &now) {
+        if (h == now) return;  // the same degrees and runs as before
+        h = std::move(now);
         d.ensure(h.size() * sizeof(int));
         HIPC(hipMemcpyAsync(d.ptr, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice, c.stream));
     };
-    up(M.dtb, M.tb);
-    up(M.dsr, M.sr);
+    up(M.dtb, M.tb, tb);
+    up(M.dsr, M.sr, sr);
 }
 
 // Items and reduction lists of the mutual pairs for a weight table.
@@ -1280,7 +1275,7 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
     // uni[i * nd + j]: the region shared by all targets of i with respect to
     // j, or -4 (one sweep over the regions in memory order)
     std::vector<int8_t> uni;
-    {
+    if (drop_pairs(c)) {
         uni.resize((size_t)c.nd * c.nd);
         for (int i = 0; i < c.nd; ++i) {
             const Drop &di = c.drops[i];
@@ -1312,7 +1307,12 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
     std::map<int, int> tslot;
     // work lists: for each (target drop i, source drop j != i): Omega_0 targets
     // against j's standard grid, Omega_1/2 targets against j's upsampled grid
-    std::vector<int> tl, k0, k1;
+    // the list's pinned image is refilled: its last upload is over
+    if (c.lists_pending) HIPC(hipStreamSynchronize(c.stream));
+    c.lists_pending = false;
+    HVec<int> &tl = c.tlist_h;
+    tl.clear();
+    std::vector<int> k0, k1;
     std::vector<PairWork> w0, w1;
     std::vector<NearItem> near;
     // (target set, source range) segments, split into work items once the
@@ -1425,10 +1425,10 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
     for (const Seg &g : segs)
         pair_items(g.grid == 0 ? w0 : w1, g.tl_off, g.cnt, g.contig, g.soff, g.ns, g.pair, g.grid, c.pair_T, CH, 0.0);
     c.tlist.ensure(std::max<size_t>(1, tl.size()) * sizeof(int));
-    if (!tl.empty())
+    if (!tl.empty()) {
         HIPC(hipMemcpyAsync(c.tlist.ptr, tl.data(), tl.size() * sizeof(int), hipMemcpyHostToDevice, c.stream));
-    HIPC(hipStreamSynchronize(c.stream));
-    c.tlist_h = std::move(tl);
+        c.lists_pending = true;
+    }
     if (!F.pairs.empty()) fmm_setup(c, cb0, cb1);
     c.w0h = std::move(w0);
     c.w1h = std::move(w1);
@@ -1437,13 +1437,26 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
 }
 
 static void run_pairs(Ctx &c, int kind, const std::vector<double> &wt);
+static Ctx::WList &work_lists(Ctx &c, const std::vector<double> &wt);
+
+// Pair passes that are only timed add into an accumulator of their own: the
+// context's may already hold the singular part of the application.
+struct TimedAcc {
+    Ctx &c;
+    explicit TimedAcc(Ctx &cc) : c(cc)
+    {
+        c.acc2.ensure((size_t)3 * c.T * sizeof(double));
+        c.acc.swap(c.acc2);
+    }
+    ~TimedAcc() { c.acc.swap(c.acc2); }
+};
 
 // Order of the fast summation chosen by timing (fmm_order = -1): the
 // double-layer pair pass (direct items plus fast summation, unit weights)
 // is timed with events at each candidate order and with every pair direct;
 // the fastest wins. For a given fmm_eps every far pair meets the same
 // truncation bound at any order, so the choice changes the cost, not the
-// accuracy. The accumulator is cleared afterwards.
+// accuracy.
 static int tune_fmm(Ctx &c, const std::vector<double> &cb0, const std::vector<double> &cb1)
 {
     static const int cand[] = {0, 8, 12, 16, 20, 24, 30};
@@ -1453,6 +1466,7 @@ static int tune_fmm(Ctx &c, const std::vector<double> &cb0, const std::vector<do
     HIPC(hipEventCreate(&e1));
     int best = 0;
     float tbest = 0.0f;
+    TimedAcc own(c);
     for (int P : cand) {
         build_lists(c, P, cb0, cb1);
         if (P > 0 && c.fmm.pairs.empty()) continue;  // no far pair at this order: the same as direct
@@ -1470,16 +1484,15 @@ static int tune_fmm(Ctx &c, const std::vector<double> &cb0, const std::vector<do
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    HIPC(hipMemsetAsync(c.acc.ptr, 0, (size_t)3 * c.T * sizeof(double), c.stream));
     return best;
 }
 
 // Work-item shape of the pair sums chosen by timing (option pair_tune):
-// targets per lane T in {1, 2, 4} and sources per item ch in {ch0/2, ch0,
-// 2 ch0} (ch0 the pair-count rule's choice for that T), double-layer pair
-// passes (unit weights, after a warm-up pass) timed with HIP events on the
-// context stream, two rounds over the candidates, the faster of each
-// candidate's two counted. The rule's own shape is kept unless a candidate
+// targets per lane T in {2, 4} and sources per item ch in {ch0/2, ch0,
+// 2 ch0} (ch0 the pair-count rule's choice for that T), besides the rule's own
+// shape; double-layer pair passes (unit weights, after a warm-up pass) timed
+// with HIP events on the context stream, the faster of a candidate's two
+// passes counted. The rule's own shape is kept unless a candidate
 // beats it by more than kTuneMargin (a single pass varies by a few percent
 // run to run; a smaller gain is not worth a shape chosen on noise). The
 // choice depends on the
@@ -1499,23 +1512,30 @@ struct PairShapeKey {
 static std::mutex g_shape_mu;
 static std::map<PairShapeKey, std::pair<int, int>> g_shapes;
 constexpr float kTuneMargin = 0.03f;
+constexpr float kTuneLongMs = 2.0f;
 
-static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std::vector<double> &cb1)
+// Returns whether the lists are built with the shape chosen.
+static bool tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std::vector<double> &cb1)
 {
-    c.pair_T_fix = 0;
-    c.pair_ch = 0;
+    // the lists are built with the shape used last in this context (the lookup
+    // below needs their number of pairs): usually the one that is found
+    c.pair_T_fix = c.last_T;
+    c.pair_ch = c.last_ch;
     build_lists(c, P, cb0, cb1);
     c.pair_tuned = true;
-    if (c.npairs_direct <= 0.0) return;
-    const int expo = (int)std::floor(std::log10(c.npairs_direct)) - 1;
-    const PairShapeKey key{(long)std::llround(c.npairs_direct / std::pow(10.0, expo)), c.T, expo, P};
+    if (c.npairs_direct <= 0.0) return true;
+    double all = c.npairs_direct;
+    for (auto &ij : c.mut.pairs) all += 2.0 * npts(c.drops[ij.first].p) * npts(c.drops[ij.second].p);
+    const int expo = (int)std::floor(std::log10(all)) - 1;
+    const PairShapeKey key{(long)std::llround(all / std::pow(10.0, expo)), c.T, expo, P};
     {
         std::lock_guard<std::mutex> lk(g_shape_mu);
         auto it = g_shapes.find(key);
         if (it != g_shapes.end()) {
-            c.pair_T_fix = it->second.first;
-            c.pair_ch = it->second.second;
-            return;
+            const bool built = c.last_T == it->second.first && c.last_ch == it->second.second;
+            c.pair_T_fix = c.last_T = it->second.first;
+            c.pair_ch = c.last_ch = it->second.second;
+            return built;
         }
     }
     const std::vector<double> ones((size_t)c.nd * c.nd, 1.0);
@@ -1542,12 +1562,21 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     }
     if (std::find(cand.begin(), cand.end(), std::make_pair(rT, rch)) == cand.end()) cand.emplace_back(rT, rch);
     std::vector<float> best(cand.size(), 0.0f);
-    for (int round = 0; round < 2; ++round)
+    TimedAcc own(c);
+    // A second round evens out what varies between passes of a few tens of
+    // microseconds; passes of kTuneLongMs are timed once (they repeat within 1 %),
+    // and a pass is warmed up where its kernel or its scratch size is new
+    // (candidates of one T: the most items first). Sixteen drops of degree 48:
+    // 21 passes of 9.6 ms became 9.
+    float longest = 0.0f;
+    for (int round = 0; round < 2 && (round == 0 || longest < kTuneLongMs); ++round)
         for (size_t k = 0; k < cand.size(); ++k) {
             c.pair_T_fix = cand[k].first;
             c.pair_ch = cand[k].second;
             build_lists(c, P, cb0, cb1);
-            if (round == 0) run_pairs(c, 1, ones);  // warm-up
+            (void)work_lists(c, ones);
+            if (round == 0 && (longest < kTuneLongMs || cand[k].first != cand[k - 1].first))
+                run_pairs(c, 1, ones);  // warm-up
             HIPC(hipEventRecord(e0, c.stream));
             run_pairs(c, 1, ones);
             HIPC(hipEventRecord(e1, c.stream));
@@ -1555,10 +1584,10 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
             float ms = 0.0f;
             HIPC(hipEventElapsedTime(&ms, e0, e1));
             best[k] = round == 0 ? ms : std::min(best[k], ms);
+            longest = std::max(longest, ms);
         }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    HIPC(hipMemsetAsync(c.acc.ptr, 0, (size_t)3 * c.T * sizeof(double), c.stream));
     size_t kr = std::find(cand.begin(), cand.end(), std::make_pair(rT, rch)) - cand.begin(), kb = kr;
     for (size_t k = 0; k < cand.size(); ++k)
         if (best[k] < best[kb]) kb = k;
@@ -1566,39 +1595,43 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     const int bestT = cand[kb].first, bestch = cand[kb].second;
     std::lock_guard<std::mutex> lk(g_shape_mu);
     const auto it = g_shapes.emplace(key, std::make_pair(bestT, bestch)).first;  // the first stored wins
-    c.pair_T_fix = it->second.first;
-    c.pair_ch = it->second.second;
+    c.pair_T_fix = c.last_T = it->second.first;
+    c.pair_ch = c.last_ch = it->second.second;
+    return false;
 }
 
-static void build_regions(Ctx &c)
+// The regions of every target are built in two parts: regions_begin enqueues
+// the nodes, the classification and the readback; regions_finish waits for
+// that readback alone and builds the pair lists on the host. What a caller
+// enqueues between the two (the singular pipeline of a single layer: it needs
+// neither the regions nor the lists) keeps the device busy meanwhile. One
+// stream does it: a second stream for the pipeline was as fast for a context
+// alone on the device, but with three contexts in use, six streams on four
+// hardware queues, sixteen drops of degree 48 took 29.5 ms against 27.2 and
+// one drop of degree 16 213 us against 188.
+static void regions_begin(Ctx &c)
 {
     if (c.regions_ok) return;
     build_nodes(c);
     // grid spacings from the volumes on the device; the volume check is read
     // back with the regions (or on its own when there are no drop pairs)
     c.hj.ensure(c.nd * sizeof(double));
-    c.hbad.ensure(sizeof(int));
-    launch_drop_h(c.stream, c.nd, c.vol.d(), c.hfac.d(), c.hj.d(), c.hbad.as<int>());
-    int bad = 0;
-    auto check_volumes = [&]() {
-        if (!bad) return;
-        std::vector<double> vol(c.nd);
-        HIPC(hipMemcpyAsync(vol.data(), c.vol.ptr, c.nd * sizeof(double), hipMemcpyDeviceToHost, c.stream));
-        HIPC(hipStreamSynchronize(c.stream));
-        for (int i = 0; i < c.nd; ++i)
-            REQUIRE(vol[i] > 0.0 && std::isfinite(vol[i]), BIM_EINVAL,
-                    "drop " + std::to_string(i) + " has non-positive volume");
-    };
-    const long nreg = c.T * c.nd;
-    c.reg.ensure(nreg);
+    const long nreg = c.T * c.nd, obad = (nreg + 7) & ~7L;  // the volume check follows the regions
+    c.reg.ensure(obad + 8);
+    int *dbad = reinterpret_cast<int *>(c.reg.as<char>() + obad);
+    launch_drop_h(c.stream, c.nd, c.vol.d(), c.hfac.d(), c.hj.d(), dbad);
     c.dist.ensure(nreg * sizeof(double));
     c.cbnd.ensure(4 * c.nd * sizeof(double));
     c.clist.ensure(std::max<long>(1, nreg) * sizeof(int));
     c.ccount.ensure(sizeof(int));
+    // drops that interact (two drops of one system); without any, the bound
+    // kernel writes every region (own drop -1, other system -2) and there is
+    // nothing to scan or to list
+    const bool pairs = drop_pairs(c), fmm = c.opt.fmm_order != 0 && pairs;
     {
         ProfScope ps(c, "classify", 0.0, 0.0);
         launch_drop_bounds(c.stream, c.nd, c.tx.d(), c.T, c.noff.as<int>(), c.ncnt.as<int>(), c.cbnd.d());
-        if (c.opt.fmm_order != 0) {
+        if (fmm) {
             c.cbnd1.ensure(4 * c.nd * sizeof(double));
             launch_drop_bounds(c.stream, c.nd, c.s1x.d(), c.S1, c.unoff.as<int>(), c.uncnt.as<int>(), c.cbnd1.d());
         }
@@ -1607,51 +1640,65 @@ static void build_regions(Ctx &c)
                               c.cbnd.d(), c.hj.d(),
                               c.opt.A_tilde, c.regions_exact ? 1 : 0, c.reg.as<int8_t>(), c.dist.d(),
                               c.clist.as<int>(), c.ccount.as<int>());
-    }
-    // drops that interact (two drops of one system); without any, the bound
-    // kernel has already written every region (own drop -1, other system -2)
-    // and there is nothing to scan or to list
-    bool pairs = false;
-    for (int i = 0; i < c.nd && !pairs; ++i)
-        for (int j = i + 1; j < c.nd; ++j)
-            if (c.sys_h[i] == c.sys_h[j]) {
-                pairs = true;
-                break;
-            }
-    if (pairs) {
-        {
-            ProfScope ps(c, "classify", 0.0, 0.0);
+        if (pairs)
             launch_classify_scan(c.stream, c.ccount.as<int>(), nreg, c.clist.as<int>(), c.nd, c.tx.d(), c.T, c.tx.d(),
                                  c.T, c.noff.as<int>(), c.ncnt.as<int>(), c.hj.d(), c.opt.A_tilde,
                                  c.reg.as<int8_t>(), c.dist.d());
-        }
-        c.reg_h.resize(nreg);
-        HIPC(hipMemcpyAsync(c.reg_h.data(), c.reg.ptr, nreg, hipMemcpyDeviceToHost, c.stream));
-        HIPC(hipMemcpyAsync(&bad, c.hbad.ptr, sizeof(int), hipMemcpyDeviceToHost, c.stream));
-        HIPC(hipStreamSynchronize(c.stream));
-    } else {
-        c.reg_h.assign(nreg, -1);  // not read without pairs
-        HIPC(hipMemcpyAsync(&bad, c.hbad.ptr, sizeof(int), hipMemcpyDeviceToHost, c.stream));
-        HIPC(hipStreamSynchronize(c.stream));
     }
-    check_volumes();
+    c.reg_h.resize(obad + 8);  // (the regions themselves are not read without pairs)
+    const long first = pairs ? 0 : obad;
+    HIPC(hipMemcpyAsync(c.reg_h.data() + first, c.reg.as<char>() + first, obad + 8 - first, hipMemcpyDeviceToHost,
+                        c.stream));
+    if (fmm) {
+        c.cb_h.resize(8 * c.nd);
+        HIPC(hipMemcpyAsync(c.cb_h.data(), c.cbnd.ptr, 4 * c.nd * sizeof(double), hipMemcpyDeviceToHost, c.stream));
+        HIPC(hipMemcpyAsync(c.cb_h.data() + 4 * c.nd, c.cbnd1.ptr, 4 * c.nd * sizeof(double), hipMemcpyDeviceToHost,
+                            c.stream));
+    }
+    if (!c.ev_reg) HIPC(hipEventCreateWithFlags(&c.ev_reg, hipEventDisableTiming));
+    HIPC(hipEventRecord(c.ev_reg, c.stream));
+    c.reg_pending = true;
+}
+
+static void regions_finish(Ctx &c)
+{
+    if (c.regions_ok) return;
+    REQUIRE(c.reg_pending, BIM_ESTATE, "regions not started");
+    c.reg_pending = false;
+    HIPC(hipEventSynchronize(c.ev_reg));
+    c.lists_pending = false;  // uploaded by an earlier evaluation: before the event
+    int bad = 0;
+    std::memcpy(&bad, c.reg_h.data() + ((c.T * c.nd + 7) & ~7L), sizeof(int));
+    if (bad) {
+        std::vector<double> vol(c.nd);
+        HIPC(hipMemcpyAsync(vol.data(), c.vol.ptr, c.nd * sizeof(double), hipMemcpyDeviceToHost, c.stream));
+        HIPC(hipStreamSynchronize(c.stream));
+        for (int i = 0; i < c.nd; ++i)
+            REQUIRE(vol[i] > 0.0 && std::isfinite(vol[i]), BIM_EINVAL,
+                    "drop " + std::to_string(i) + " has non-positive volume");
+    }
+    const bool pairs = drop_pairs(c);
     std::vector<double> cb0, cb1;
     if (c.opt.fmm_order != 0 && pairs) {
-        cb0.resize(4 * c.nd);
-        cb1.resize(4 * c.nd);
-        HIPC(hipMemcpyAsync(cb0.data(), c.cbnd.ptr, cb0.size() * sizeof(double), hipMemcpyDeviceToHost, c.stream));
-        HIPC(hipMemcpyAsync(cb1.data(), c.cbnd1.ptr, cb1.size() * sizeof(double), hipMemcpyDeviceToHost, c.stream));
-        HIPC(hipStreamSynchronize(c.stream));
+        cb0.assign(c.cb_h.begin(), c.cb_h.begin() + 4 * c.nd);
+        cb1.assign(c.cb_h.begin() + 4 * c.nd, c.cb_h.begin() + 8 * c.nd);
     }
     int P = pairs ? c.opt.fmm_order : 0;
     if (P < 0) {
         if (c.fmm_tuned < 0) c.fmm_tuned = tune_fmm(c, cb0, cb1);
         P = c.fmm_tuned;
     }
-    if (c.opt.pair_tune && pairs && !c.pair_tuned) tune_pairs(c, P, cb0, cb1);
-    build_lists(c, P, cb0, cb1);
+    bool built = false;
+    if (c.opt.pair_tune && pairs && !c.pair_tuned) built = tune_pairs(c, P, cb0, cb1);
+    if (!built) build_lists(c, P, cb0, cb1);
     near_setup(c);
     c.regions_ok = true;
+}
+
+static void build_regions(Ctx &c)
+{
+    regions_begin(c);
+    regions_finish(c);
 }
 
 // Device work lists for a weight table wt[i * nd + j] (items of zero weight
@@ -1761,8 +1808,15 @@ static void pack32(Ctx &c, int kind, const PairSrc &g0, const PairSrc &g1)
                        c.rec32_1.as<float4>());
 }
 
+// Whether there are pair sums other than the nearest-region items'.
+static bool pair_sums(const Ctx &c)
+{
+    return !c.w0h.empty() || !c.w1h.empty() || !c.mut.pairs.empty() || !c.fmm.pairs.empty();
+}
+
 static void run_pairs(Ctx &c, int kind, const std::vector<double> &wt)
 {
+    if (!pair_sums(c)) return;
     Ctx::WList &L = work_lists(c, wt);
     const double fpp = kind == 0 ? 29.0 : 30.0;  // flops per pair (SL / DL)
     const PairSrc g0{c.tx.d(), c.s0N.d(), c.s0W.d(), c.s0d.d(), c.T};
@@ -2173,14 +2227,10 @@ static bool pipe_fits(int p, int qs)
 // the batched pipeline: single layer of dens added into acc (sl) and/or the
 // stored double-layer rows of each drop (dl). Chunks are sets of (drop,
 // latitude) units sized by a memory budget for the intermediates.
-// st: the stream of the launches (the context's by default); acc_out: where
-// the single layer's longitude sums are added (acc by default).
-static void run_pipe_group(Ctx &c, const std::vector<int> &ids, bool sl, bool dl, const double *dens,
-                           hipStream_t st = nullptr, double *acc_out = nullptr)
+static void run_pipe_group(Ctx &c, const std::vector<int> &ids, bool sl, bool dl, const double *dens)
 {
     if (ids.empty()) return;
-    if (!st) st = c.stream;
-    if (!acc_out) acc_out = c.acc.d();
+    hipStream_t st = c.stream;
     const Drop &d0 = c.drops[ids[0]];
     const int p = d0.p, qs = d0.qs, P1 = p + 1, Q1 = qs + 1, nk = 2 * p, nc = ncoef(p);
     RotTab &r = rot(c, p);
@@ -2230,14 +2280,14 @@ static void run_pipe_group(Ctx &c, const std::vector<int> &ids, bool sl, bool dl
         const int nuc = std::min(nj, nu - u0);
         const long nt = (long)nuc * nk, NC6 = nt * 6, NC12 = nt * 12;
         {
-            ProfScope ps(c, "pipe_rotate", nt * (sl ? 6.0 : 3.0) * rotlat * 4.0, nt * (sl ? 2.0 : 1.0) * nc * 6 * 8.0, st);
+            ProfScope ps(c, "pipe_rotate", nt * (sl ? 6.0 : 3.0) * rotlat * 4.0, nt * (sl ? 2.0 : 1.0) * nc * 6 * 8.0);
             launch_rot2(st, p, r.Ap.d(), r.Am.d(), gp.cs.d(), c.xc.d(), c.Ctot, sl ? dens : nullptr, c.Ctot,
                         pd, u0, nuc, c.pBx.d(), sl ? c.pBd.d() : nullptr, NC6);
             launch_pole(st, p, (int)nt, c.pBx.d(), NC6, c.pX0.d());
         }
         {
             ProfScope ps(c, "pipe_legendre", 2.0 * 2 * Q1 * nc * NC6 + (sl ? 2.0 * Q1 * nc * NC6 : 0.0),
-                         8.0 * ((double)nc * NC6 * (sl ? 2 : 1) + (double)P1 * 2 * Q1 * NC6 + (sl ? (double)P1 * Q1 * NC6 : 0.0)), st);
+                         8.0 * ((double)nc * NC6 * (sl ? 2 : 1) + (double)P1 * 2 * Q1 * NC6 + (sl ? (double)P1 * Q1 * NC6 : 0.0)));
             launch_leg_mfma(st, P1, pt.maxrows_syn, pt.bsx.ptr, pt.syn.d(), c.pBx.d(), c.pGx.d(), NC6);
             if (sl) launch_leg_mfma(st, P1, Q1, pt.bsd.ptr, pt.syn.d(), c.pBd.d(), c.pGd.d(), NC6);
         }
@@ -2254,18 +2304,18 @@ static void run_pipe_group(Ctx &c, const std::vector<int> &ids, bool sl, bool dl
             double fl = fft * (sl ? 12.0 : 9.0) + (sl ? NP * 35.0 : 0.0);
             if (dl) fl += NP * 40.0 + 6.0 * fft;
             ProfScope ps(c, "pipe_fourier", nt * fl,
-                         8.0 * ((double)P1 * (sl ? 3 : 2) * Q1 * NC6 + (dl ? (double)P1 * Q1 * NC12 : 0.0)), st);
+                         8.0 * ((double)P1 * (sl ? 3 : 2) * Q1 * NC6 + (dl ? (double)P1 * Q1 * NC12 : 0.0)));
             launch_fk(st, sl, dl, p, qs, (int)nt, c.pGx.d(), sl ? c.pGd.d() : nullptr, NC6, gs.wsing.d(),
                       gs.cs.d(), c.pX0.d(), c.pPart.d(), dl ? c.pFa.d() : nullptr, NC12);
-            if (sl) launch_sum_part(st, (int)nt, Q1, nk, P1, c.pPart.d(), pd, u0, 1.0, acc_out, c.T);
+            if (sl) launch_sum_part(st, (int)nt, Q1, nk, P1, c.pPart.d(), pd, u0, 1.0, c.acc.d(), c.T);
         }
         if (dl) {
             {
-                ProfScope ps(c, "pipe_legendre", 2.0 * Q1 * nc * NC12, 8.0 * ((double)P1 * Q1 * NC12 + (double)nc * NC12), st);
+                ProfScope ps(c, "pipe_legendre", 2.0 * Q1 * nc * NC12, 8.0 * ((double)P1 * Q1 * NC12 + (double)nc * NC12));
                 launch_leg_mfma(st, P1, pt.maxrows_ana, pt.ban.ptr, pt.ana.d(), c.pFa.d(), c.pBt.d(), NC12);
             }
             {
-                ProfScope ps(c, "pipe_adjrot", nt * 6.0 * rotlat * 4.0, 8.0 * ((double)nc * NC12 + (double)nt * 6 * 2 * nc), st);
+                ProfScope ps(c, "pipe_adjrot", nt * 6.0 * rotlat * 4.0, 8.0 * ((double)nc * NC12 + (double)nt * 6 * 2 * nc));
                 launch_adjrot(st, p, r.Ap.d(), r.Am.d(), gp.cs.d(), c.pBt.d(), NC12, pd, u0, nuc);
             }
         }
@@ -2410,61 +2460,10 @@ static void double_layer_grid(Ctx &c, const double *ucoef, const std::vector<dou
     run_near(c, 1, ucoef, wt);
 }
 
-// Whether two drops of one system interact (there are pair sums).
-static bool drop_pairs(const Ctx &c)
-{
-    for (int i = 0; i < c.nd; ++i)
-        for (int j = i + 1; j < c.nd; ++j)
-            if (c.sys_h[i] == c.sys_h[j]) return true;
-    return false;
-}
-
-// Whether a choice by timing (pair work shape, fast-summation order,
-// transform path) is still to be made: its timed launches must not share the
-// device with other work.
-static bool timing_pending(const Ctx &c)
-{
-    const bool f32 = c.opt.precision == BIM_PREC_MIXED;
-    if (c.opt.xform_path == 0 && (c.xmode[0][f32] < 0 || c.xmode[1][f32] < 0)) return true;
-    if (!drop_pairs(c)) return false;
-    return (c.opt.pair_tune && !c.pair_tuned) || (c.opt.fmm_order < 0 && c.fmm_tuned < 0);
-}
-
-// The context's stream waits for the work of the second stream (a no-op
-// when nothing is pending there).
-static void join_side(Ctx &c)
-{
-    if (!c.join_pending) return;
-    c.join_pending = false;
-    HIPC(hipStreamWaitEvent(c.stream, c.ev_join, 0));
-}
-
-// Orders the second stream after the work enqueued so far on the context's
-// stream (creating the stream and its events on first use).
-static void fork_side(Ctx &c)
-{
-    join_side(c);
-    if (!c.side) {
-        HIPC(hipStreamCreateWithFlags(&c.side, hipStreamNonBlocking));
-        HIPC(hipEventCreateWithFlags(&c.ev_fork, hipEventDisableTiming));
-        HIPC(hipEventCreateWithFlags(&c.ev_join, hipEventDisableTiming));
-    }
-    HIPC(hipEventRecord(c.ev_fork, c.stream));
-    HIPC(hipStreamWaitEvent(c.side, c.ev_fork, 0));
-}
-
 // Single layer of fcoef at all targets into acc. with_dl[i] also builds the
 // stored double-layer rows of drop i in the same pass; wt_dl: the weights of
 // the double-layer operator that will follow, whose pair lists are built
-// while the device runs the pipeline.
-//
-// The singular pipeline needs neither the regions nor the node densities.
-// When the regions are still to be built, it runs on the second stream,
-// adding into acc2, while the context's stream classifies the regions and
-// the host builds the pair lists (with no timing pending, whose launches
-// must have the device to themselves). acc then starts as a copy of acc2:
-// the same values, added in the same order, as when the pipeline adds into a
-// cleared acc on the context's stream.
+// while the device runs the pair sums of this one.
 static void single_layer_grid(Ctx &c, const double *fcoef, const std::vector<char> *with_dl = nullptr,
                               const std::vector<double> *wt_dl = nullptr)
 {
@@ -2475,32 +2474,12 @@ static void single_layer_grid(Ctx &c, const double *fcoef, const std::vector<cha
         const bool dl = with_dl && (*with_dl)[i] && !dl_matrix_ready(c, i);
         (dl ? with_rows : without_rows).push_back(i);
     }
-    const bool side = !c.regions_ok && !(with_rows.empty() && without_rows.empty()) && !timing_pending(c);
-    const size_t accb = (size_t)3 * c.T * sizeof(double);
-    if (side) {
-        c.acc2.ensure(accb);
-        fork_side(c);
-        HIPC(hipMemsetAsync(c.acc2.ptr, 0, accb, c.side));
-        for (auto &g : pipe_groups(c, with_rows)) run_pipe_group(c, g, true, true, fcoef, c.side, c.acc2.d());
-        for (auto &g : pipe_groups(c, without_rows)) run_pipe_group(c, g, true, false, fcoef, c.side, c.acc2.d());
-        HIPC(hipEventRecord(c.ev_join, c.side));
-        c.join_pending = true;
-    }
-    build_regions(c);
+    regions_begin(c);
     std::vector<double> wt((size_t)c.nd * c.nd, 1.0);
-    if (side) {
-        (void)work_lists(c, wt);  // uploads enqueued now run beside the pipeline
-        if (wt_dl) (void)work_lists(c, *wt_dl);
-    }
     std::vector<char> need(c.nd, 1);
     density_nodes(c, fcoef, need, false, c.acc.d(), 3 * c.T);  // acc cleared by the same launch
-    if (side) {
-        join_side(c);
-        HIPC(hipMemcpyAsync(c.acc.ptr, c.acc2.ptr, accb, hipMemcpyDeviceToDevice, c.stream));
-    } else {
-        for (auto &g : pipe_groups(c, with_rows)) run_pipe_group(c, g, true, true, fcoef);
-        for (auto &g : pipe_groups(c, without_rows)) run_pipe_group(c, g, true, false, fcoef);
-    }
+    for (auto &g : pipe_groups(c, with_rows)) run_pipe_group(c, g, true, true, fcoef);
+    for (auto &g : pipe_groups(c, without_rows)) run_pipe_group(c, g, true, false, fcoef);
     for (int i = 0; i < c.nd; ++i) {
         const Drop &d = c.drops[i];
         const bool dl = with_dl && (*with_dl)[i] && !dl_matrix_ready(c, i);
@@ -2514,10 +2493,12 @@ static void single_layer_grid(Ctx &c, const double *fcoef, const std::vector<cha
             run_singular(c, i, 0, fcoef, 1.0);
         }
     }
+    regions_finish(c);
     if (!c.near_h.empty())
         HIPC(hipMemcpyAsync(c.near_self.ptr, c.acc.ptr, 3 * c.T * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
     run_pairs(c, 0, wt);
     run_near(c, 0, fcoef, wt);
+    if (wt_dl && (pair_sums(c) || !c.near_h.empty())) (void)work_lists(c, *wt_dl);
 }
 
 // analysis of grid vectors [3][T] into coefficients [3][Ctot]
@@ -2553,33 +2534,21 @@ static void apply_operator(Ctx &c, const double *x, double *y, const std::vector
 {
     double_layer_grid(c, x, wt);
     // y = (lambda + 1) x - P[acc]: the combine rides on the analysis (the
-    // scalar one when every drop's grid fits it)
+    // scalar one takes every degree a drop may have)
     auto run = [&](bool mfma) {
         if (mfma) {
             xanal_drops(c, c.acc.d(), x, y, true);
             return;
         }
         std::vector<AnaJob> jobs;
-        bool fused = true;
         for (int i = 0; i < c.nd; ++i) {
             const Drop &d = c.drops[i];
             AnaJob j = ana_job(c, d.p, d.p, 3, c.acc.d() + d.toff, c.T, y + d.coff, c.Ctot);
             j.cx = x + d.coff;
             j.csc = d.lam + 1.0;
-            fused = fused && anal_batch_lds(d.p, d.p) <= 163840;
             jobs.push_back(j);
         }
-        if (fused) {
-            ana_run(c, jobs);
-        } else {
-            std::vector<AnaJob> pj;
-            for (int i = 0; i < c.nd; ++i) {
-                const Drop &d = c.drops[i];
-                pj.push_back(ana_job(c, d.p, d.p, 3, c.acc.d() + d.toff, c.T, y + d.coff, c.Ctot));
-            }
-            ana_run(c, pj);
-            launch_op_combine(c.stream, 3 * c.Ctot, c.scl.d(), x, y);
-        }
+        ana_run(c, jobs);
     };
     run(xform_mfma(c, 1, c.opt.precision == BIM_PREC_MIXED, run));
 }
@@ -2770,6 +2739,65 @@ static void invalidate(Ctx &c)
     std::fill(c.Mok.begin(), c.Mok.end(), 0);
 }
 
+// Tables that hang on the degrees of the drops alone (offsets, counts, the
+// drop of each target, grid spacing factors, Gauss-Legendre nodes): parts of
+// one device buffer, uploaded in one copy when the degrees change. They were
+// eleven copies of 3 us and as many calls at every bim_set_drops.
+static void degree_tables(Ctx &c)
+{
+    std::vector<int> ps(c.nd);
+    for (int i = 0; i < c.nd; ++i) ps[i] = c.drops[i].p;
+    if (ps == c.tab_p) return;
+    c.tab_p.clear();
+    c.last_T = c.last_ch = 0;  // another problem: its work shape is not this one's
+    const int nd = c.nd;
+    c.voloff_h.assign(nd + 1, 0);
+    std::vector<int> tdrop(c.T), noff(nd), ncnt(nd), unoff(nd), uncnt(nd), gloff(nd);
+    std::vector<long> dcoff(nd);
+    std::vector<double> hfac(nd), glt;
+    for (int i = 0; i < nd; ++i) {
+        const Drop &d = c.drops[i];
+        c.voloff_h[i + 1] = c.voloff_h[i] + (npts(d.p) + 63) / 64;
+        for (int t = 0; t < npts(d.p); ++t) tdrop[d.toff + t] = i;
+        noff[i] = (int)d.toff;
+        ncnt[i] = npts(d.p);
+        unoff[i] = (int)d.uoff;
+        uncnt[i] = npts(d.qu);
+        hfac[i] = kPi / (d.p + 1);
+        dcoff[i] = d.coff;
+        gloff[i] = (int)glt.size();
+        const GridTab &g = grid(c, d.p, d.p);
+        glt.insert(glt.end(), g.t.begin(), g.t.end());
+    }
+    // 8-byte entries first
+    std::vector<std::pair<DBuf *, std::pair<const void *, size_t>>> parts;
+    auto add = [&](DBuf &d, const auto &v) { parts.push_back({&d, {v.data(), v.size() * sizeof(v[0])}}); };
+    add(c.hfac, hfac);
+    add(c.near_glt, glt);
+    add(c.near_dcoff, dcoff);
+    add(c.noff, noff);
+    add(c.ncnt, ncnt);
+    add(c.unoff, unoff);
+    add(c.uncnt, uncnt);
+    add(c.near_gloff, gloff);
+    add(c.near_dp, ps);
+    add(c.near_dtoff, noff);
+    add(c.voloff, c.voloff_h);
+    add(c.tdrop, tdrop);
+    size_t n = 0;
+    for (auto &p : parts) n += p.second.second;
+    c.h_tab.resize(n);
+    c.tab.ensure(n);
+    n = 0;
+    for (auto &p : parts) {
+        std::memcpy(c.h_tab.data() + n, p.second.first, p.second.second);
+        p.first->part_of(c.tab.as<char>() + n, p.second.second);
+        n += p.second.second;
+    }
+    HIPC(hipMemcpyAsync(c.tab.ptr, c.h_tab.data(), n, hipMemcpyHostToDevice, c.stream));
+    c.tab_p = ps;
+}
+
 static void require_drops(Ctx &c) { REQUIRE(c.nd > 0, BIM_ESTATE, "no drops set (call bim_set_drops first)"); }
 
 template <class F> static int guarded(Ctx *c, F &&f)
@@ -2777,9 +2805,6 @@ template <class F> static int guarded(Ctx *c, F &&f)
     if (!c) return BIM_EINVAL;
     try {
         HIPC(hipSetDevice(c->device));
-        // work left on the second stream by a call that failed midway is
-        // ordered before anything this call enqueues
-        join_side(*c);
         int rc = f();
         if (rc == BIM_OK) c->err.clear();
         return rc;
@@ -2980,6 +3005,9 @@ int bim_set_drops(bim_ctx h, int n_drops, const int *p, const double *xcoef, con
             std::memcpy(hx.data(), xcoef, hx.size() * sizeof(double));
         }
         for (double v : hx) REQUIRE(std::isfinite(v), BIM_EINVAL, "non-finite surface coefficient");
+        // the pinned images are refilled: their last uploads are over
+        if (c.upload_pending) HIPC(hipStreamSynchronize(c.stream));
+        c.upload_pending = false;
         c.nd = n_drops;
         c.drops = ds;
         c.xplans.clear();
@@ -2989,15 +3017,20 @@ int bim_set_drops(bim_ctx h, int n_drops, const int *p, const double *xcoef, con
         c.Ctot = coff;
         c.T = toff;
         c.S1 = uoff;
-        // uploads from pinned host images: enqueued without waiting, all
-        // complete at the synchronisation that ends this call
-        auto up = [&](DBuf &d, auto &img) {
-            d.ensure(std::max<size_t>(1, img.size()) * sizeof(img[0]));
-            if (!img.empty())
-                HIPC(hipMemcpyAsync(d.ptr, img.data(), img.size() * sizeof(img[0]), hipMemcpyHostToDevice, c.stream));
-        };
+        invalidate(c);
+        // tables for every grid in use
+        for (auto &d : ds) {
+            grid(c, d.p, d.p);
+            grid(c, d.qu, d.p);
+            grid(c, d.qg, d.p);
+            grid(c, d.qs, d.p);
+            rot(c, d.p);
+        }
+        // uploads from pinned host images, enqueued without waiting
         c.h_xc.assign(hx.begin(), hx.end());
-        up(c.xc, c.h_xc);
+        c.xc.ensure(c.h_xc.size() * sizeof(double));
+        c.upload_pending = true;
+        HIPC(hipMemcpyAsync(c.xc.ptr, c.h_xc.data(), c.h_xc.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
         c.gc.ensure((size_t)coff * sizeof(double));
         HIPC(hipMemsetAsync(c.gc.ptr, 0, (size_t)coff * sizeof(double), c.stream));
         c.fc.ensure((size_t)3 * coff * sizeof(double));
@@ -3017,49 +3050,17 @@ int bim_set_drops(bim_ctx h, int n_drops, const int *p, const double *xcoef, con
         c.tmp.ensure((size_t)3 * c.T * sizeof(double));
         c.bvec.ensure((size_t)3 * c.Ctot * sizeof(double));
         c.xsol.ensure((size_t)3 * c.Ctot * sizeof(double));
-        HVec<int> &tdrop = c.h_tdrop, &noff = c.h_noff, &ncnt = c.h_ncnt, &unoff = c.h_unoff, &uncnt = c.h_uncnt;
-        tdrop.resize(c.T);
-        noff.resize(c.nd);
-        ncnt.resize(c.nd);
-        unoff.resize(c.nd);
-        uncnt.resize(c.nd);
-        for (int i = 0; i < c.nd; ++i) {
-            for (int t = 0; t < npts(ds[i].p); ++t) tdrop[ds[i].toff + t] = i;
-            noff[i] = (int)ds[i].toff;
-            ncnt[i] = npts(ds[i].p);
-            unoff[i] = (int)ds[i].uoff;
-            uncnt[i] = npts(ds[i].qu);
-        }
         c.sys_h.assign(c.nd, 0);
-        c.h_sys.assign(c.nd, 0);
-        up(c.sysd, c.h_sys);
-        up(c.tdrop, tdrop);
-        up(c.noff, noff);
-        up(c.ncnt, ncnt);
-        c.h_hfac.resize(c.nd);
-        for (int i = 0; i < c.nd; ++i) c.h_hfac[i] = kPi / (ds[i].p + 1);
-        up(c.hfac, c.h_hfac);
-        up(c.unoff, unoff);
-        up(c.uncnt, uncnt);
-        // Galerkin operator diagonal (lambda_i + 1)
-        HVec<double> &scl = c.h_scl;
-        scl.resize((size_t)3 * c.Ctot);
-        for (int comp = 0; comp < 3; ++comp)
-            for (int i = 0; i < c.nd; ++i)
-                for (long e = 0; e < 2L * ncoef(ds[i].p); ++e) scl[comp * c.Ctot + ds[i].coff + e] = ds[i].lam + 1.0;
-        up(c.scl, scl);
-        c.h_gU.assign(c.gradU, c.gradU + 9);
-        up(c.gU, c.h_gU);
-        invalidate(c);
-        // tables for every grid in use
-        for (auto &d : ds) {
-            grid(c, d.p, d.p);
-            grid(c, d.qu, d.p);
-            grid(c, d.qg, d.p);
-            grid(c, d.qs, d.p);
-            rot(c, d.p);
+        if (c.sys_up != c.sys_h) {
+            c.sysd.ensure(c.nd * sizeof(int));
+            HIPC(hipMemsetAsync(c.sysd.ptr, 0, c.nd * sizeof(int), c.stream));
+            c.sys_up = c.sys_h;
         }
-        HIPC(hipStreamSynchronize(c.stream));
+        if (!c.gU.ptr) {  // the far field has not been set
+            c.gU.ensure(9 * sizeof(double));
+            HIPC(hipMemsetAsync(c.gU.ptr, 0, 9 * sizeof(double), c.stream));
+        }
+        degree_tables(c);
         return BIM_OK;
     });
 }
@@ -3074,6 +3075,7 @@ int bim_set_systems(bim_ctx h, const int *system_of_drop)
         c.sys_h.assign(system_of_drop, system_of_drop + c.nd);
         HIPC(hipMemcpyAsync(c.sysd.ptr, c.sys_h.data(), c.nd * sizeof(int), hipMemcpyHostToDevice, c.stream));
         HIPC(hipStreamSynchronize(c.stream));
+        c.sys_up = c.sys_h;
         c.regions_ok = false;
         c.regions_exact = false;
         c.fmm_tuned = -1;  // other drop pairs: choose the fast-summation order again
@@ -3173,8 +3175,12 @@ int bim_single_layer(bim_ctx h, const double *f_coef, double *out, int mem_kind)
             dens = c.fc.d();
         }
         single_layer_grid(c, dens);
-        launch_scale_add(c.stream, 3 * c.T, -1.0 / (8.0 * kPi), c.acc.d(), 0.0, c.acc.d());
-        copy_out(c, out, c.acc.ptr, (size_t)3 * c.T * sizeof(double), mem_kind);
+        if (mem_kind == BIM_MEM_DEVICE) {
+            launch_scale_add(c.stream, 3 * c.T, -1.0 / (8.0 * kPi), c.acc.d(), 0.0, out);
+        } else {
+            launch_scale_add(c.stream, 3 * c.T, -1.0 / (8.0 * kPi), c.acc.d(), 0.0, c.acc.d());
+            copy_out(c, out, c.acc.ptr, (size_t)3 * c.T * sizeof(double), mem_kind);
+        }
         return BIM_OK;
     });
 }
@@ -3661,8 +3667,9 @@ int bim_apply_double_layer_noalloc(bim_ctx h, const double *u_coef, double *out,
         const Ctx::WList *L = nullptr;
         for (auto &e : c.wlists)
             if (!e->stale && e->wt == wt) L = e.get();
-        REQUIRE(L, BIM_ESTATE, "the pair work list of this mode is not built: apply bim_apply_double_layer once first");
-        const double need = std::max((double)L->n * 3 * 64 * c.pair_T, (double)c.near_nwork * 3 * 64);
+        REQUIRE(L || !(pair_sums(c) || !c.near_h.empty()), BIM_ESTATE,
+                "the pair work list of this mode is not built: apply bim_apply_double_layer once first");
+        const double need = std::max(L ? (double)L->n * 3 * 64 * c.pair_T : 0.0, (double)c.near_nwork * 3 * 64);
         REQUIRE(need <= (double)kScratchDoubles, BIM_ENOMEM,
                 "the pair partial sums need " + std::to_string((long)(need * 8 / (1 << 20))) +
                     " MiB, above the " + std::to_string((long)(kScratchDoubles * 8 >> 20)) + " MiB scratch");

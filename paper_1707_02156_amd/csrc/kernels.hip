@@ -830,14 +830,6 @@ __global__ void k_scale_add(long n, double a, const double *__restrict__ x, doub
     if (i < n) y[i] = b == 0.0 ? a * x[i] : a * x[i] + b * y[i];
 }
 
-// y_i = s_i * x_i - y_i with s_i = (lambda_drop(i) + 1): the Galerkin operator
-// (lambda + 1) u - P[D u], entries grouped by a per-entry scale array.
-__global__ void k_op_combine(long n, const double *__restrict__ sc, const double *__restrict__ x, double *__restrict__ y)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = sc[i] * x[i] - y[i];
-}
-
 // ----------------------------------------------------------------------------
 // Gram-Schmidt passes of the Arnoldi step. A block owns kGsChunk entries of w
 // (kGsR per lane, in registers); its four wavefronts split the basis vectors
@@ -1340,11 +1332,6 @@ void launch_rhs(hipStream_t st, int T, const double *tx, long tstride, const dou
 void launch_scale_add(hipStream_t st, long n, double a, const double *x, double b, double *y)
 {
     hipLaunchKernelGGL(k_scale_add, dim3(nblk(n)), dim3(256), 0, st, n, a, x, b, y);
-}
-
-void launch_op_combine(hipStream_t st, long n, const double *sc, const double *x, double *y)
-{
-    hipLaunchKernelGGL(k_op_combine, dim3(nblk(n)), dim3(256), 0, st, n, sc, x, y);
 }
 
 long gs_blocks(long n) { return (n + kGsChunk - 1) / kGsChunk; }
