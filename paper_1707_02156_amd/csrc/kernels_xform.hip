@@ -4,16 +4,18 @@
 // for many (drop, grid, field) jobs in one launch; the job list travels in the
 // kernel arguments.
 //
-// Synthesis block = (job, latitude j, range of 64 longitudes): Legendre sums G[c][kind][m] =
+// Synthesis block = (job, component, latitudes j and q - j, range of 64 longitudes): Legendre sums G[kind][m] =
 // sum_n c_n^m L_kind(t_j) for the kinds the requested derivatives need, into
-// LDS; then each thread forms points k and k + q of one output field with the
-// even/odd split e^{i m (phi + pi)} = (-1)^m e^{i m phi}.
+// LDS; then two lanes form points k, k + q, -k and q - k of one output field with
+// the even/odd split e^{i m (phi + pi)} = (-1)^m e^{i m phi}.
 // Analysis block = (job, component, chunk of four orders m): F[j][m] =
 // sum_k v_jk e^{-i m phi_k} into LDS, then f_n^m = sum_j (pi/q) w_j h_m
 // Ptilde_n^m(t_j) F[j][m] with h_q = 1/2 (grids up to q = 512).
 #include "internal.hpp"
 
 #include <hip/hip_runtime.h>
+
+#include <mutex>
 
 namespace bim {
 
@@ -39,93 +41,195 @@ struct SynJobs {
 
 constexpr int kSynK = 64;  // longitudes k <= q/2 (and their images k + q, -k, q - k) per synthesis block
 
-__global__ __launch_bounds__(256) void k_synth_batch(SynJobs jobs)
+constexpr int kSynThreads = 320;
+// two doubles of an array that is aligned as doubles are
+typedef double synd2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// Longitudes [k0, k0 + kn) and their images of component c from the Legendre
+// sums G of latitudes j and q - j (orders m > 0 with their factor of two): four
+// lanes per output field and longitude, each with the orders of one residue mod 4 and
+// one of the four images.
+template <bool VALUES> __device__ inline void synth_longitudes(const SynJob &J, int c, int j, int k0, int kn,
+                                                                const double2 *G)
 {
-    __shared__ double G[3 * 3 * 65 * 2];  // [c][kind][m][re,im]
+    const int tid = threadIdx.x, p = J.p, P1 = p + 1, q = J.q, nk = 2 * q, mask = J.mask;
+    const int nout = VALUES ? 1 : __popc(mask);
+    const double qi = 1.0 / q;
+    const int s = tid & 3, nf = nout * kn, items = j < q - j ? 2 * nf : nf;
+    for (int i0 = 0; i0 < items; i0 += kSynThreads / 4) {
+        const int it = i0 + (tid >> 2), ic = min(it, items - 1);
+        const int half = ic >= nf, r = ic - half * nf;
+        const int fo = VALUES ? 0 : r / kn, k = k0 + r - fo * kn;
+        int dt = 0, dp = 0;
+        if (!VALUES) {
+            int b = 0, cnt = 0;  // the fo-th field of the mask
+#pragma unroll
+            for (int x = 0; x < 6; ++x)
+                if (mask >> x & 1) {
+                    b = cnt == fo ? x : b;
+                    ++cnt;
+                }
+            dt = 388 >> 2 * b & 3;   // kDt, kDp, two bits each
+            dp = 2320 >> 2 * b & 3;
+        }
+        // d/dphi: (a, b) -> (-m b, m a); d2/dphi2: -m^2 (a, b)
+        const double *g = reinterpret_cast<const double *>(G + (half * 3 + dt) * P1), *ga = g + (dp == 1),
+                     *gb = g + (dp != 1);
+        const double f0 = dp == 0 ? 1.0 : 0.0, f1 = dp == 1 ? 1.0 : 0.0, f2 = dp == 2 ? -1.0 : 0.0,
+                     sa = dp == 1 ? -1.0 : 1.0;
+        double s1, c1;
+        sincospi(qi * k, &s1, &c1);
+        // orders m = s, s + 4, ..: cosine and sine sums kept apart (C - S at phi,
+        // C + S at -phi); the odd orders flip at phi + pi
+        const double c2 = fma(c1, c1, -(s1 * s1)), s2 = 2.0 * s1 * c1;
+        const double c4 = fma(c2, c2, -(s2 * s2)), s4 = 2.0 * s2 * c2;
+        const double ce = s & 2 ? c2 : 1.0, se = s & 2 ? s2 : 0.0;
+        double cm = s & 1 ? ce * c1 - se * s1 : ce, sm = s & 1 ? fma(se, c1, ce * s1) : se, C = 0.0, S = 0.0, md = s;
+#pragma unroll 4
+        for (int m = s; m <= p; m += 4) {
+            double ar = ga[2 * m], ai = gb[2 * m];
+            if (!VALUES) {
+                const double f = fma(md, fma(md, f2, f1), f0);
+                ar *= sa * f;
+                ai *= f;
+                md += 4.0;
+            }
+            C = fma(ar, cm, C);
+            S = fma(ai, sm, S);
+            const double t = cm * c4 - sm * s4;
+            sm = fma(sm, c4, cm * s4);
+            cm = t;
+        }
+        C += __shfl_xor(C, 2, 64);
+        S += __shfl_xor(S, 2, 64);
+        const double Co = __shfl_xor(C, 1, 64), So = __shfl_xor(S, 1, 64);
+        // even and odd orders, with the sign of the lane's image
+        const double E = (s & 1 ? Co : C) + (s & 2 ? (s & 1 ? So : S) : -(s & 1 ? So : S));
+        const double O = (s & 1 ? C : Co) + (s & 2 ? (s & 1 ? S : So) : -(s & 1 ? S : So));
+        if (it >= items) continue;
+        double *o = J.out + fo * J.fstride + c * J.ostride + (long)(half ? q - j : j) * nk;
+        if (s == 0) o[k] = E + O;                              // phi_k
+        if (s == 1) o[k + q] = E - O;                          // phi_k + pi
+        if (s == 2 && k > 0 && 2 * k != q) o[nk - k] = E + O;  // -phi_k
+        if (s == 3 && k > 0 && 2 * k != q) o[q - k] = E - O;   // pi - phi_k
+    }
+}
+
+// Component c, latitudes j and q - j, longitudes [z kSynK, (z + 1) kSynK) of
+// job J; the two latitudes are mirrored (t -> -t), so that they share the
+// Legendre entries: the terms with n + m odd change sign (for d/dtheta those
+// with n + m even). LDS: Legendre sums G [latitude][kind][m], then the component's coefficients and the
+// latitudes' Legendre entries of the kinds in use.
+//
+// Latency-bound: a block has some thousand FMAs. What costs is the way to the
+// coefficients, which every block reads and another XCD has just written, so
+// they come in once, neighbouring lanes neighbouring entries, all loads in
+// flight together; an order's sum is spread over up to eight lanes, a
+// longitude's over four. Read from memory where they are used, by one lane per
+// order of one latitude, two drops' densities on both grids took 14.1 us at
+// degree 32 and 8.1 at degree 16, 48 derivative fields of degree 31 15.3 us;
+// so 9.1, 5.6 and 13.8 (one latitude per block: 9.2, 5.4 and 16.2).
+template <bool STAGED> __device__ inline void synth_block(const SynJob &J, int c, int j, int z, double2 *G)
+{
+    const int tid = threadIdx.x;
+    const int p = J.p, P1 = p + 1, q = J.q, nc = P1 * (p + 2) / 2;
+    const int k0 = z * kSynK;
+    const int H = q / 2 + 1;  // longitudes k <= q/2; the others by symmetry
+    if (c >= J.ncomp || 2 * j > q || k0 >= H) return;
+    const int kn = min(kSynK, H - k0);
+    // bit 0: Ptilde, 1: d/dtheta, 2: d2/dtheta2 (kDt)
+    const int kinds = ((J.mask & 0x25) ? 1 : 0) | ((J.mask & 0x12) ? 2 : 0) | ((J.mask & 8) ? 4 : 0);
+    const int nki = __popc(kinds), kl0 = __ffs(kinds) - 1, kl1 = kinds == 5 ? 2 : kl0 + 1;
+    synd2 *cs = reinterpret_cast<synd2 *>(G + 6 * P1);
+    double *ls = reinterpret_cast<double *>(cs + nc);
+    const synd2 *cf = reinterpret_cast<const synd2 *>(J.coef + c * J.cstride);
+    const double *L0 = J.L + (long)j * J.ldn;
+    const long lk = (long)(q + 1) * J.ldn;
+    if (STAGED) {
+        for (int e0 = tid; e0 < nc; e0 += 4 * kSynThreads) {
+            synd2 v[4];
+            double l[3][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = min(e0 + u * kSynThreads, nc - 1);
+                v[u] = cf[e];
+                l[0][u] = L0[kl0 * lk + e];
+                if (nki > 1) l[1][u] = L0[kl1 * lk + e];
+                if (nki > 2) l[2][u] = L0[2 * lk + e];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = e0 + u * kSynThreads;
+                if (e >= nc) break;
+                cs[e] = v[u];
+                ls[e] = l[0][u];
+                if (nki > 1) ls[nc + e] = l[1][u];
+                if (nki > 2) ls[2 * nc + e] = l[2][u];
+            }
+        }
+    }
+    __syncthreads();
+    const int items = nki * P1;
+    // lanes per order, an even number: a lane's terms have one parity of n - m
+    const int lg = items * 8 <= kSynThreads ? 3 : items * 4 <= kSynThreads ? 2 : 1;
+    for (int i0 = 0; i0 < items; i0 += kSynThreads >> lg) {
+        const int sub = tid & ((1 << lg) - 1), it = i0 + (tid >> lg), ic = min(it, items - 1);
+        const int ki = ic / P1, m = ic - ki * P1, kind = ki == 0 ? kl0 : ki == 1 ? kl1 : 2;
+        const double *l = STAGED ? ls + ki * nc : L0 + kind * lk;
+        double sr = 0.0, si = 0.0;
+#pragma unroll 4
+        for (int n = m + sub; n <= p; n += 1 << lg) {
+            const int e = n * (n + 1) / 2 + m;
+            const synd2 v = STAGED ? cs[e] : cf[e];
+            sr = fma(v.x, l[e], sr);
+            si = fma(v.y, l[e], si);
+        }
+        for (int o = 2; o < 1 << lg; o <<= 1) {
+            sr += __shfl_xor(sr, o, 64);
+            si += __shfl_xor(si, o, 64);
+        }
+        const double tr = __shfl_xor(sr, 1, 64), ti = __shfl_xor(si, 1, 64);
+        const double w = m ? 2.0 : 1.0;  // orders m and -m
+        // sub 0: the sum at t_j; sub 1: at -t_j, the terms of the changing parity subtracted
+        if (it < items) {
+            if (sub == 0) G[kind * P1 + m] = make_double2(w * (sr + tr), w * (si + ti));
+            if (sub == 1) {
+                const double v = kind == 1 ? w : -w;
+                G[(3 + kind) * P1 + m] = make_double2(v * (sr - tr), v * (si - ti));
+            }
+        }
+    }
+    __syncthreads();
+    // values only (the densities of an operator application): no derivative factors
+    if (J.mask == 1)
+        synth_longitudes<true>(J, c, j, k0, kn, G);
+    else
+        synth_longitudes<false>(J, c, j, k0, kn, G);
+}
+
+// STAGED: coefficients and Legendre entries fit the LDS (degrees to 111 with
+// values or one derivative); else they are read where they are used.
+template <bool STAGED> __global__ __launch_bounds__(kSynThreads) void k_synth_batch(SynJobs jobs)
+{
+    extern __shared__ double2 G[];
     {
         const long nb = (long)gridDim.x * gridDim.y * gridDim.z;
         const long bid = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
         for (int z = 0; z < 2; ++z)
             if (jobs.zero[z])
-                for (long i = bid * 256 + threadIdx.x; i < jobs.nzero[z]; i += nb * 256) jobs.zero[z][i] = 0.0;
+                for (long i = bid * kSynThreads + threadIdx.x; i < jobs.nzero[z]; i += nb * kSynThreads)
+                    jobs.zero[z][i] = 0.0;
     }
     const SynJob &J = jobs.j[blockIdx.y];
-    const int j = blockIdx.x;
-    const int k0 = blockIdx.z * kSynK;
-    const int H = J.q / 2 + 1;  // longitudes k <= q/2; the others by symmetry
-    if (j > J.q || k0 >= H) return;
-    const int kn = min(kSynK, H - k0);
-    const int p = J.p, P1 = p + 1, q = J.q, nk = 2 * q;
-    int kinds = 0;  // bit 0: Ptilde, 1: d/dtheta, 2: d2/dtheta2
-    for (int b = 0; b < 6; ++b)
-        if (J.mask >> b & 1) kinds |= 1 << kDt[b];
-    const int nq = J.q + 1;
-    for (int it = threadIdx.x; it < J.ncomp * 3 * P1; it += 256) {
-        const int m = it % P1;
-        const int r = it / P1;
-        const int kind = r % 3, c = r / 3;
-        if (!(kinds >> kind & 1)) continue;
-        const double *cf = J.coef + c * J.cstride;
-        const double *Lj = J.L + ((long)kind * nq + j) * J.ldn;
-        double sr = 0.0, si = 0.0;
-        int e = m * (m + 1) / 2 + m;
-#pragma unroll 4
-        for (int n = m; n <= p; ++n) {
-            const double l = Lj[e];
-            sr = fma(cf[2 * e], l, sr);
-            si = fma(cf[2 * e + 1], l, si);
-            e += n + 1;
-        }
-        G[2 * ((c * 3 + kind) * P1 + m)] = sr;
-        G[2 * ((c * 3 + kind) * P1 + m) + 1] = si;
-    }
-    __syncthreads();
-    int nout = 0, fidx[6];
-    for (int b = 0; b < 6; ++b)
-        if (J.mask >> b & 1) fidx[nout++] = b;
-    const double dphi = 3.14159265358979323846 / q;
-    for (int it = threadIdx.x; it < J.ncomp * nout * kn; it += 256) {
-        const int k = k0 + it % kn;
-        const int r = it / kn;
-        const int fo = r % nout, c = r / nout;
-        const int b = fidx[fo], dt = kDt[b], dp = kDp[b];
-        const double *g = G + 2 * ((c * 3 + dt) * P1);
-        double sn, cs;
-        sincos(dphi * k, &sn, &cs);
-        // cosine and sine sums kept apart (C - S at phi, C + S at -phi) and
-        // split by the parity of m (the odd orders flip at phi + pi)
-        double cm = 1.0, sm = 0.0, ce = 0.0, co = 0.0, se = 0.0, so = 0.0;
-        for (int m = 0; m <= p; ++m) {
-            double ar = g[2 * m], ai = g[2 * m + 1];
-            if (dp == 1) {
-                const double t = -m * ai;
-                ai = m * ar;
-                ar = t;
-            } else if (dp == 2) {
-                ar *= -(double)m * m;
-                ai *= -(double)m * m;
-            }
-            const double w = m ? 2.0 : 1.0;
-            const double vc = w * ar * cm, vs = w * ai * sm;
-            if (m & 1) {
-                co += vc;
-                so += vs;
-            } else {
-                ce += vc;
-                se += vs;
-            }
-            const double c2 = cm * cs - sm * sn;
-            sm = fma(sm, cs, cm * sn);
-            cm = c2;
-        }
-        double *o = J.out + fo * J.fstride + c * J.ostride + (long)j * nk;
-        o[k] = (ce - se) + (co - so);      // phi_k
-        o[k + q] = (ce - se) - (co - so);  // phi_k + pi
-        if (k > 0 && 2 * k != q) {
-            o[nk - k] = (ce + se) + (co + so);  // -phi_k
-            o[q - k] = (ce + se) - (co + so);   // pi - phi_k
-        }
-    }
+    synth_block<STAGED>(J, blockIdx.z % 3, blockIdx.x, blockIdx.z / 3, G);
+}
+
+// LDS of a synthesis block: its sums, coefficients and Legendre entries
+static size_t synth_lds(const SynJob &J)
+{
+    const int kinds = ((J.mask & 0x25) != 0) + ((J.mask & 0x12) != 0) + ((J.mask & 8) != 0);
+    const size_t nc = (size_t)(J.p + 1) * (J.p + 2) / 2;
+    return 6 * (size_t)(J.p + 1) * 16 + nc * (16 + 8 * kinds);
 }
 
 constexpr int kMaxAnaJobs = 24;
@@ -211,12 +315,27 @@ void launch_synth_batch(hipStream_t st, const SynJob *jobs, int n, double *z0, l
             b.zero[1] = nz1 > 0 ? z1 : nullptr;
             b.nzero[1] = nz1;
         }
-        int maxq = 0;
+        int maxq = 0, maxp = 0;
+        size_t lds = 0;
         for (int i = 0; i < b.n; ++i) {
             b.j[i] = jobs[o + i];
             maxq = std::max(maxq, jobs[o + i].q);
+            maxp = std::max(maxp, jobs[o + i].p);
+            lds = std::max(lds, synth_lds(jobs[o + i]));
         }
-        hipLaunchKernelGGL(k_synth_batch, dim3(maxq + 1, b.n, (maxq / 2 + 1 + kSynK - 1) / kSynK), dim3(256), 0, st, b);
+        const dim3 nb(maxq / 2 + 1, b.n, 3 * ((maxq / 2 + 1 + kSynK - 1) / kSynK));
+        if (lds > 163840) {
+            hipLaunchKernelGGL(k_synth_batch<false>, nb, dim3(kSynThreads), 6 * (size_t)(maxp + 1) * 16, st, b);
+            continue;
+        }
+        if (lds > 65536) {
+            static std::once_flag once;  // concurrent callers wait until the limit is set
+            std::call_once(once, [] {
+                (void)hipFuncSetAttribute((const void *)k_synth_batch<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          163840);
+            });
+        }
+        hipLaunchKernelGGL(k_synth_batch<true>, nb, dim3(kSynThreads), lds, st, b);
     }
 }
 
