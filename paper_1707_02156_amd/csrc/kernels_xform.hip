@@ -41,7 +41,7 @@ struct SynJobs {
 
 constexpr int kSynK = 64;  // longitudes k <= q/2 (and their images k + q, -k, q - k) per synthesis block
 
-constexpr int kSynThreads = 320;
+constexpr int kSynThreads = 256;
 // two doubles of an array that is aligned as doubles are
 typedef double synd2 __attribute__((ext_vector_type(2), aligned(8)));
 
@@ -128,7 +128,10 @@ template <bool VALUES> __device__ inline void synth_longitudes(const SynJob &J, 
 // longitude's over four. Read from memory where they are used, by one lane per
 // order of one latitude, two drops' densities on both grids took 14.1 us at
 // degree 32 and 8.1 at degree 16, 48 derivative fields of degree 31 15.3 us;
-// so 9.1, 5.6 and 13.8 (one latitude per block: 9.2, 5.4 and 16.2).
+// so 8.3, 5.5 and 10.3. A block has one wavefront per SIMD: a larger one waits
+// for room while the pair sums of another context fill the device (three
+// contexts in turn, four drops of degree 32: 145 us per operator application
+// with 256 threads, 156 with 320).
 template <bool STAGED> __device__ inline void synth_block(const SynJob &J, int c, int j, int z, double2 *G)
 {
     const int tid = threadIdx.x;
