@@ -113,6 +113,9 @@ struct SynJob {
 };
 void launch_synth_batch(hipStream_t st, const SynJob *jobs, int n, double *z0 = nullptr, long nz0 = 0,
                         double *z1 = nullptr, long nz1 = 0);
+bool synth_rows_fits(const SynJob *jobs, int n, int rows);
+void launch_synth_rows(hipStream_t st, const SynJob *jobs, int n, const DlJob *rows, int nrows, long ustride,
+                       long ostride);
 void launch_anal_batch(hipStream_t st, const AnaJob *jobs, int n);
 size_t anal_batch_lds(int p, int q);
 bool xform_fits(int p, int q, bool analysis);
@@ -120,8 +123,6 @@ void launch_xsynth(hipStream_t st, bool f32, const XJob *jobs, int n, const doub
                    double *z1, long nz1);
 void launch_xanal(hipStream_t st, bool f32, const XJob *jobs, int n, const double *x, double *y, double sgn);
 bool sing_fused_fits(int p, int qs, bool sl, bool dl);
-void launch_dl_apply(hipStream_t st, int nt, int nc2, const double *M, const double *u, long ustride, double w,
-                     double *out, long ostride);
 void launch_rhs(hipStream_t st, int T, const double *tx, long tstride, const double *s, double a, const double *U0,
                 const double *gU_dev, double *b);
 void launch_scale_add(hipStream_t st, long n, double a, const double *x, double b, double *y);
@@ -2115,11 +2116,17 @@ static void xanal_drops(Ctx &c, const double *gridv, const double *x, double *y,
 // the double-layer operator); the force density of the single layer stays
 // FP64: its layer is the sum of terms that nearly cancel for a drop close to
 // equilibrium, and FP32 node values would set the error of that small sum.
-static void density_nodes(Ctx &c, const double *dens, const std::vector<char> &need, bool f32, double *z0 = nullptr,
-                          long nz0 = 0, double *z1 = nullptr, long nz1 = 0)
+//
+// rows: stored-row products of the density for every target of acc, written by
+// the same launch where the batched path is taken and one launch holds them;
+// returns whether they were (else z0, z1 have been cleared and they are left
+// to the caller).
+static bool density_nodes(Ctx &c, const double *dens, const std::vector<char> &need, bool f32, double *z0 = nullptr,
+                          long nz0 = 0, double *z1 = nullptr, long nz1 = 0, const std::vector<DlJob> *rows = nullptr)
 {
+    bool with_rows = false;
     f32 = f32 && c.opt.precision == BIM_PREC_MIXED;
-    auto run = [&](bool mfma) {
+    auto run = [&](bool mfma, const std::vector<DlJob> *rw = nullptr) {
         if (mfma) {
             std::vector<XJob> xj;
             size_t goff = 0;
@@ -2137,9 +2144,16 @@ static void density_nodes(Ctx &c, const double *dens, const std::vector<char> &n
             jobs.push_back(syn_job(c, d.p, d.p, 3, dens + d.coff, c.Ctot, 0x1, c.s0d.d() + d.toff, c.T, 0));
             jobs.push_back(syn_job(c, d.p, d.qu, 3, dens + d.coff, c.Ctot, 0x1, c.s1d.d() + d.uoff, c.S1, 0));
         }
+        if (rw && synth_rows_fits(jobs.data(), (int)jobs.size(), (int)rw->size())) {
+            launch_synth_rows(c.stream, jobs.data(), (int)jobs.size(), rw->data(), (int)rw->size(), c.Ctot, c.T);
+            with_rows = true;
+            return;
+        }
         syn_run(c, jobs, z0, nz0, z1, nz1);
     };
-    run(xform_mfma(c, 0, f32, run));
+    const bool mfma = xform_mfma(c, 0, f32, run);
+    run(mfma, rows);
+    return with_rows;
 }
 
 // Singular self-integral of drop i with density coefficients dens [3][Ctot]
@@ -2414,39 +2428,52 @@ static void double_layer_grid(Ctx &c, const double *ucoef, const std::vector<dou
             if (wt[(size_t)i * c.nd + j] != 0.0) need[j] = 1;
     for (const NearItem &it : c.near_h)
         if (wt[(size_t)it.i * c.nd + it.j] != 0.0) selfraw[it.j] = 1;
-    // acc (and near_self) cleared by the density synthesis launch
-    density_nodes(c, ucoef, need, true, c.acc.d(), 3 * c.T, c.near_h.empty() ? nullptr : c.near_self.d(),
-                  c.near_h.empty() ? 0 : 3 * c.T);
     // stored rows: build those missing (pipeline drops grouped by degree)
     std::vector<int> build;
     for (int i = 0; i < c.nd; ++i) {
         const Drop &d = c.drops[i];
-        if ((wt[(size_t)i * c.nd + i] != 0.0 || selfraw[i]) && use_pipe(c, d) && !dl_matrix_ready(c, i))
-            build.push_back(i);
+        if ((wt[(size_t)i * c.nd + i] != 0.0 || selfraw[i]) && !dl_matrix_ready(c, i)) {
+            if (use_pipe(c, d))
+                build.push_back(i);
+            else if (use_fused(c, d, false, true))
+                run_fused(c, i, false, true, nullptr);
+        }
     }
     for (auto &g : pipe_groups(c, build)) run_pipe_group(c, g, false, true, nullptr);
-    std::vector<DlJob> jobs;
+    std::vector<DlJob> jobs, all(c.nd);
     double dfl = 0.0, dby = 0.0;
+    bool stored = true;
     for (int i = 0; i < c.nd; ++i) {
         const double w = wt[(size_t)i * c.nd + i];
-        if (w == 0.0 && !selfraw[i]) continue;
         const Drop &d = c.drops[i];
         // the raw self-interaction goes to near_self when an item interpolates from it
         double *dst = selfraw[i] ? c.near_self.d() : c.acc.d();
-        const double ws = selfraw[i] ? 1.0 : w;
+        all[i] = DlJob{nullptr, nullptr, dst + d.toff, 0.0, npts(d.p), 0};
+        if (w == 0.0 && !selfraw[i]) continue;
         if (use_pipe(c, d) || use_fused(c, d, false, true)) {
-            if (!dl_matrix_ready(c, i)) run_fused(c, i, false, true, nullptr);
             const double nt = npts(d.p), nc2 = 2.0 * ncoef(d.p);
             dfl += nt * 18.0 * nc2;
             dby += nt * 6.0 * nc2 * 8.0 + 3.0 * nc2 * 8.0;
-            jobs.push_back(DlJob{c.Mdl[i]->d(), ucoef + d.coff, dst + d.toff, ws, npts(d.p), 2 * ncoef(d.p)});
+            all[i] = DlJob{c.Mdl[i]->d(), ucoef + d.coff, dst + d.toff, selfraw[i] ? 1.0 : w, npts(d.p), 2 * ncoef(d.p)};
+            jobs.push_back(all[i]);
         } else {
-            run_singular(c, i, 1, ucoef, ws, dst);
+            stored = false;
         }
     }
-    if (!jobs.empty()) {
-        ProfScope ps(c, "dl_apply", dfl, dby);
-        launch_dl_apply_multi(c.stream, jobs.data(), (int)jobs.size(), c.Ctot, c.T);
+    // every self-interaction from stored rows (or absent) and into acc: in the
+    // launch of the density synthesis (two launches when launches are timed one
+    // by one); else acc (and near_self) are cleared by that launch and added to
+    const bool near = !c.near_h.empty();
+    const bool joint = stored && !near && !jobs.empty() && !c.prof_on;
+    if (!density_nodes(c, ucoef, need, true, c.acc.d(), 3 * c.T, near ? c.near_self.d() : nullptr, near ? 3 * c.T : 0,
+                       joint ? &all : nullptr)) {
+        if (!jobs.empty()) {
+            ProfScope ps(c, "dl_apply", dfl, dby);
+            launch_dl_apply_multi(c.stream, jobs.data(), (int)jobs.size(), c.Ctot, c.T);
+        }
+        for (int i = 0; i < c.nd; ++i)
+            if (!all[i].M && (wt[(size_t)i * c.nd + i] != 0.0 || selfraw[i]))
+                run_singular(c, i, 1, ucoef, selfraw[i] ? 1.0 : wt[(size_t)i * c.nd + i], all[i].out - c.drops[i].toff);
     }
     for (int i = 0; i < c.nd; ++i) {
         const double w = wt[(size_t)i * c.nd + i];
