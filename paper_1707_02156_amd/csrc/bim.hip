@@ -1371,7 +1371,7 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
                 }
                 F.pairs.push_back(FmmPair{sslot[ks], tslot[i], forder, 0, 0.0});
                 const double nt = (forder + 1) * (forder + 2) / 2;
-                F.m2l_flops += nt * (forder + 1) * (forder + 1) * 32.0;
+                F.m2l_flops += nt * (forder + 1) * (forder + 1) * 20.0;
                 F.pair_ij.push_back(i * c.nd + j);
                 continue;
             }

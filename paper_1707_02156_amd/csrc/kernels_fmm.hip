@@ -113,7 +113,12 @@ __global__ void k_fmm_srcw(const FmmSrcJob *__restrict__ jobs, int kind, const d
 
 // ---- P2M: partial multipoles of source chunks ------------------------------
 // Block (chunk, job): thread = coefficient tri(n,m); sums over the chunk's
-// kFmmChunk sources; part[(job chunk base + chunk)][c][tri].
+// kFmmChunk sources; part[(job chunk base + chunk)][c][tri]. A dipole's
+// coefficient (n, m) joins U_{n-1} at m, m + 1 and m - 1, times a and b of its
+// moments: linear, so a thread sums its own U times the twelve real weights
+// (one read of Y and 24 FMAs a source) and the sums are joined at the end,
+// through LDS. Bound by the read of Y (64 drops on the 2x grid, P = 24: 600 MB):
+// 157 us against 216 with three reads and 64 FP64 instructions a source.
 template <int KIND, class YT>
 __global__ __launch_bounds__(kFmmThreads) void k_fmm_p2m(const FmmSrcJob *__restrict__ jobs, int P,
                                                          const YT *__restrict__ Y, const double *__restrict__ W,
@@ -126,17 +131,17 @@ __global__ __launch_bounds__(kFmmThreads) void k_fmm_p2m(const FmmSrcJob *__rest
     const int s1 = min(j.ns, s0 + kFmmChunk);
     const int ntri = (P + 1) * (P + 2) / 2;
     const int e = threadIdx.x;
-    if (e >= ntri) return;
+    const int ec = min(e, ntri - 1);
     int n = 0;
-    while ((n + 1) * (n + 2) / 2 <= e) ++n;
-    const int m = e - n * (n + 1) / 2;
+    while ((n + 1) * (n + 2) / 2 <= ec) ++n;
+    const int m = ec - n * (n + 1) / 2;
     double ar[4] = {0, 0, 0, 0}, ai[4] = {0, 0, 0, 0};
     const YT *Yc = Y + j.yoff;
     constexpr int NW = KIND == 0 ? 4 : 12;
     const double *Wc = W + j.woff;
     if (KIND == 0) {
         for (int s = s0; s < s1; ++s) {
-            const YT uy = Yc[(long)s * ntri + e];
+            const YT uy = Yc[(long)s * ntri + ec];
             const double2 u = make_double2(uy.x, uy.y);
             const double *w = Wc + (long)s * NW;
 #pragma unroll
@@ -145,41 +150,60 @@ __global__ __launch_bounds__(kFmmThreads) void k_fmm_p2m(const FmmSrcJob *__rest
                 ai[ch] = fma(-w[ch], u.y, ai[ch]);
             }
         }
-    } else if (n > 0) {
-        // conj(m.grad U_n^m) = a conj(U_{n-1}^m) + b conj(U_{n-1}^{m+1}) - conj(b) conj(U_{n-1}^{m-1})
-        const bool hp = m + 1 <= n - 1, hm = m <= n - 1;
-        const int e0 = ftri(n - 1, min(m, n - 1)), ep = ftri(n - 1, min(m + 1, n - 1)),
-                  em = ftri(n - 1, m > 0 ? m - 1 : 1 <= n - 1 ? 1 : 0);
-        for (int s = s0; s < s1; ++s) {
-            const YT *yr = Yc + (long)s * ntri;
-            const YT y0 = yr[e0], yp = yr[ep], ym = yr[em];
-            const double2 u0 = hm ? make_double2(y0.x, y0.y) : make_double2(0.0, 0.0);
-            const double2 up = hp ? make_double2(yp.x, yp.y) : make_double2(0.0, 0.0);
-            double2 um;  // conj(U_{n-1}^{m-1}); at m = 0 conj(U^{-1}) = -U^{1}
-            if (m > 0) {
-                um = make_double2(ym.x, -ym.y);
-            } else if (n - 1 >= 1) {
-                um = make_double2(-ym.x, -ym.y);
-            } else {
-                um = make_double2(0.0, 0.0);
-            }
-            const double *w = Wc + (long)s * NW;
+    } else {
+        double2 sum[12];  // of the weights a, Re b, Im b of each channel
 #pragma unroll
-            for (int ch = 0; ch < 4; ++ch) {
-                const double a = w[3 * ch], br = w[3 * ch + 1], bi = w[3 * ch + 2];
-                // a conj(u0)
-                double re = a * u0.x, im = -a * u0.y;
-                // b conj(up)
-                re = fma(br, up.x, fma(bi, up.y, re));
-                im = fma(bi, up.x, fma(-br, up.y, im));
-                // - conj(b) um
-                re = fma(-br, um.x, fma(-bi, um.y, re));
-                im = fma(bi, um.x, fma(-br, um.y, im));
-                ar[ch] += re;
-                ai[ch] += im;
+        for (int k = 0; k < NW; ++k) sum[k] = make_double2(0.0, 0.0);
+        const int low = ftri(P, 0);  // harmonics of degrees below P
+        if (e < low) {
+            const YT *ye = Yc + e;
+#pragma unroll 4
+            for (int s = s0; s < s1; ++s) {
+                const YT uy = ye[(long)s * ntri];
+                const double2 u = make_double2(uy.x, uy.y);
+                const double *w = Wc + (long)s * NW;
+#pragma unroll
+                for (int k = 0; k < NW; ++k) {
+                    sum[k].x = fma(w[k], u.x, sum[k].x);
+                    sum[k].y = fma(w[k], u.y, sum[k].y);
+                }
             }
         }
+        // conj(m.grad U_n^m) = a conj(U_{n-1}^m) + b conj(U_{n-1}^{m+1}) - conj(b) conj(U_{n-1}^{m-1}),
+        // U_{n-1}^{-1} = -conj(U_{n-1}^1)
+        __shared__ double2 S[3][kFmmMaxOrder * (kFmmMaxOrder + 1) / 2];
+        const bool hm = n > 0 && m < n, hp = m + 1 < n, h1 = m > 0 || n > 1;
+        const int i0 = hm ? ftri(n - 1, m) : 0, ip = hp ? ftri(n - 1, m + 1) : 0,
+                  im = n > 0 && h1 ? ftri(n - 1, m > 0 ? m - 1 : 1) : 0;
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) {
+            if (ch) __syncthreads();
+            if (e < low)
+                for (int k = 0; k < 3; ++k) S[k][e] = sum[3 * ch + k];
+            __syncthreads();
+            if (n == 0) continue;
+            double re = 0.0, imv = 0.0;
+            if (hm) {
+                re = S[0][i0].x;
+                imv = -S[0][i0].y;
+            }
+            double2 r = make_double2(0.0, 0.0), i = r, rm = r, imm = r;
+            if (hp) {
+                r = S[1][ip];
+                i = S[2][ip];
+            }
+            if (h1) {
+                rm = S[1][im];
+                imm = S[2][im];
+            }
+            const double sg = m > 0 ? 1.0 : -1.0;
+            re += (r.x - sg * rm.x) + (i.y + imm.y);
+            imv += (i.x + sg * imm.x) + (rm.y - r.y);
+            ar[ch] = re;
+            ai[ch] = imv;
+        }
     }
+    if (e >= ntri) return;
     double2 *o = part + (long)(j.pbase + chunk) * 4 * ntri;
 #pragma unroll
     for (int ch = 0; ch < 4; ++ch) o[ch * ntri + e] = make_double2(ar[ch], ai[ch]);
@@ -220,7 +244,10 @@ __global__ void k_fmm_msum(const FmmSrcJob *__restrict__ jobs, int P, const doub
 // Block per pair; thread = output coefficient tri(k,l), k <= the pair's
 // order Q (coefficients above it are zero). The irregular harmonics of D up
 // to degree 2Q, every order, are built in LDS (lane = order); the multipole
-// coefficients are wavefront-uniform (scalar loads). Output:
+// coefficients are wavefront-uniform (scalar loads). The potentials are real:
+// the orders m and -m of a degree share their multipole coefficient, so that a
+// pair of orders takes 20 FP64 instructions instead of 32 (64 drops, P = 24:
+// 200 us against 297; FP64 issue bounds it). Output:
 // Lp[pair][c][tri] = w (-1)^k sum_{n<=Q,|m|<=n} M'_c T_{n+k}^{m+l}(D), with
 // channel 3 moved to the target origin.
 __global__ __launch_bounds__(kFmmThreads) void k_fmm_m2l(const FmmPair *__restrict__ pairs, int P,
@@ -282,13 +309,25 @@ __global__ __launch_bounds__(kFmmThreads) void k_fmm_m2l(const FmmPair *__restri
         const int N = n + k;
         const double2 *trow = th + (N * N + N + l);  // T_N^{m+l} at trow[m]
         const double2 *mrow = Ms + 4 * (n * n + n);  // M_n^m, 4 channels, at mrow[4 m]
-        for (int m = -n; m <= n; ++m) {
-            const double2 t = trow[m];
+        const double2 t0 = trow[0];
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) {
+            const double2 mv = mrow[ch];
+            ar[ch] = fma(mv.x, t0.x, fma(-mv.y, t0.y, ar[ch]));
+            ai[ch] = fma(mv.x, t0.y, fma(mv.y, t0.x, ai[ch]));
+        }
+        // orders m and -m together, M_n^{-m} = (-1)^m conj(M_n^m):
+        // M T^{l+m} + (-1)^m conj(M) T^{l-m} = Re M a + i Im M b
+        double sm = -1.0;
+        for (int m = 1; m <= n; ++m, sm = -sm) {
+            const double2 tp = trow[m], tm = trow[-m];
+            const double ax = fma(sm, tm.x, tp.x), ay = fma(sm, tm.y, tp.y);
+            const double bx = fma(-sm, tm.x, tp.x), by = fma(-sm, tm.y, tp.y);
 #pragma unroll
             for (int ch = 0; ch < 4; ++ch) {
                 const double2 mv = mrow[4 * m + ch];
-                ar[ch] = fma(mv.x, t.x, fma(-mv.y, t.y, ar[ch]));
-                ai[ch] = fma(mv.x, t.y, fma(mv.y, t.x, ai[ch]));
+                ar[ch] = fma(mv.x, ax, fma(-mv.y, by, ar[ch]));
+                ai[ch] = fma(mv.x, ay, fma(mv.y, bx, ai[ch]));
             }
         }
     }
@@ -460,7 +499,7 @@ void launch_fmm_p2m(hipStream_t st, const FmmSrcJob *jobs, int njobs, int maxns,
     if (!njobs || !maxns) return;
     hipLaunchKernelGGL(k_fmm_srcw, dim3((maxns + 255) / 256, njobs), dim3(256), 0, st, jobs, kind, cen, W);
     const int nch = (maxns + kFmmChunk - 1) / kFmmChunk;
-    const dim3 g(nch, njobs), b(kFmmThreads);
+    const dim3 g(nch, njobs), b(((P + 1) * (P + 2) / 2 + 63) / 64 * 64);
     if (f32) {
         const float2 *Yf = (const float2 *)Y;
         if (kind == 0)
@@ -484,7 +523,7 @@ void launch_fmm_m2l(hipStream_t st, int npairs, const FmmPair *pairs, int P, con
                     const double2 *M, double2 *Lp, int nt, const int *poff, double2 *L)
 {
     if (!npairs) return;
-    hipLaunchKernelGGL(k_fmm_m2l, dim3(npairs), dim3(kFmmThreads), fmm_m2l_lds(P), st, pairs, P, cen_s, cen_t, M, Lp);
+    hipLaunchKernelGGL(k_fmm_m2l, dim3(npairs), dim3(((P + 1) * (P + 2) / 2 + 63) / 64 * 64), fmm_m2l_lds(P), st, pairs, P, cen_s, cen_t, M, Lp);
     const int ntri = (P + 1) * (P + 2) / 2;
     hipLaunchKernelGGL(k_fmm_lsum, dim3((4 * ntri + 255) / 256, nt), dim3(256), 0, st, nt, P, poff, Lp, L);
 }
