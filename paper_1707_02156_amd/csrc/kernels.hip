@@ -7,6 +7,7 @@
 //     1 = d/dtheta, 2 = d^2/dtheta^2, j = 0..q (theta ascending);
 //   grid values: [field][j * 2q + k];
 //   cos/sin table of a degree-q grid: cs[i] = cos(pi i / q), cs[2q + i] = sin(pi i / q).
+#include "gather.hpp"
 #include "internal.hpp"
 
 #include <hip/hip_runtime.h>
@@ -755,54 +756,28 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_pair32(const PairWork *__re
 // are tent[e] + t for e in [toff[k], toff[k+1]), k = tile_of[t] (tile_of may
 // be null: no such items). Items over an index list are listed per target:
 // slots ent[e], e in [off[t], off[t+1]). Each slot holds three components at
-// stride `tile`. One wavefront per target: lane l adds the entries l, l + 64,
-// ... of the two lists in turn, then a butterfly over the lanes. Targets
-// with no slot are left alone.
+// stride `tile`. The work split: gather.hpp. Targets with no slot are left alone.
 __global__ __launch_bounds__(256) void k_pair_gather(int nt, int tile, const int *__restrict__ tile_of,
                                                      const int *__restrict__ toff, const int *__restrict__ tent,
                                                      const int *__restrict__ off, const int *__restrict__ ent,
                                                      const double *__restrict__ part, double *__restrict__ out,
                                                      long ostride, int add)
 {
-    const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    if (t >= nt) return;
+    const int t = blockIdx.x * kGatherTargets + (threadIdx.x & 15), tc = min(t, nt - 1);
     int k0 = 0, k1 = 0;
     if (tile_of) {
-        const int k = tile_of[t];
+        const int k = tile_of[tc];
         k0 = toff[k];
         k1 = toff[k + 1];
     }
-    const int e0 = off[t], e1 = off[t + 1];
-    if (k0 == k1 && e0 == e1) return;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int e = k0 + lane; e < k1; e += 64) {
-        const double *p = part + ((long)tent[e] + t);
-        s0 += p[0];
-        s1 += p[tile];
-        s2 += p[2 * tile];
-    }
-    for (int e = e0 + lane; e < e1; e += 64) {
-        const double *p = part + (long)ent[e];
-        s0 += p[0];
-        s1 += p[tile];
-        s2 += p[2 * tile];
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        s0 += __shfl_xor(s0, o, 64);
-        s1 += __shfl_xor(s1, o, 64);
-        s2 += __shfl_xor(s2, o, 64);
-    }
-    if (lane == 0) {
-        if (add) {
-            s0 += out[t];
-            s1 += out[ostride + t];
-            s2 += out[2 * ostride + t];
-        }
-        out[t] = s0;
-        out[ostride + t] = s1;
-        out[2 * ostride + t] = s2;
-    }
+    const int e0 = off[tc], e1 = off[tc + 1];
+    double s[3] = {0.0, 0.0, 0.0};
+    gather_slots(s, tent, k0, k1, tc, part, tile);
+    gather_slots(s, ent, e0, e1, 0, part, tile);
+    const double v = gather_groups(s);
+    if (threadIdx.x >= 3 * kGatherTargets || t >= nt || (k0 == k1 && e0 == e1)) return;
+    double *o = out + (threadIdx.x >> 4) * ostride + t;
+    *o = add ? v + *o : v;
 }
 
 // ----------------------------------------------------------------------------
@@ -1319,7 +1294,7 @@ void launch_pair_gather(hipStream_t st, int nt, int tile, const int *tile_of, co
                         const int *off, const int *ent, const double *part, double *out, long ostride, bool add)
 {
     if (nt <= 0) return;
-    hipLaunchKernelGGL(k_pair_gather, dim3((nt + 3) / 4), dim3(256), 0, st, nt, tile, tile_of, toff, tent, off, ent,
+    hipLaunchKernelGGL(k_pair_gather, dim3((nt + kGatherTargets - 1) / kGatherTargets), dim3(256), 0, st, nt, tile, tile_of, toff, tent, off, ent,
                        part, out, ostride, add ? 1 : 0);
 }
 

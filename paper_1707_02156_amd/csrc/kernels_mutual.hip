@@ -26,6 +26,7 @@
 // to four pairs; with them a lane holds 48 doubles, which leaves three
 // wavefronts per SIMD. That launch: 3.3 ms against 4.1 for the same pairs in
 // k_pair; the single layer's 3.1 against 3.9.
+#include "gather.hpp"
 #include "internal.hpp"
 
 #include <hip/hip_runtime.h>
@@ -205,47 +206,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 }
 
 // out[c][t] += the sums of the mutual items of target t, in a fixed order: the
-// slots of its block of targets, then those of its run of sources. One
-// wavefront per target, as in k_pair_gather. Targets with no slot are left
-// alone.
+// slots of its block of targets, then those of its run of sources (gather.hpp).
+// Targets with no slot are left alone.
 __global__ __launch_bounds__(256) void k_mutual_gather(int nt, MutualGather mg, const double *__restrict__ part,
                                                        double *__restrict__ out, long ostride)
 {
-    const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    if (t >= nt) return;
-    const int a = mg.tb[t], b = mg.sr[t];
+    const int t = blockIdx.x * kGatherTargets + (threadIdx.x & 15), tc = min(t, nt - 1);
+    const int a = mg.tb[tc], b = mg.sr[tc];
     const int a0 = mg.toff[a], a1 = mg.toff[a + 1], b0 = mg.soff[b], b1 = mg.soff[b + 1];
-    if (a0 == a1 && b0 == b1) return;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int e = a0 + lane; e < a1; e += 64) {
-        const double *p = part + ((long)mg.tent[e] + t);
-        s0 += p[0];
-        s1 += p[kMutTargets];
-        s2 += p[2 * kMutTargets];
-    }
-    for (int e = b0 + lane; e < b1; e += 64) {
-        const double *p = part + ((long)mg.sent[e] + t);
-        s0 += p[0];
-        s1 += p[mg.R];
-        s2 += p[2L * mg.R];
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        s0 += __shfl_xor(s0, o, 64);
-        s1 += __shfl_xor(s1, o, 64);
-        s2 += __shfl_xor(s2, o, 64);
-    }
-    if (lane == 0) {
-        out[t] += s0;
-        out[ostride + t] += s1;
-        out[2 * ostride + t] += s2;
-    }
+    double s[3] = {0.0, 0.0, 0.0};
+    gather_slots(s, mg.tent, a0, a1, tc, part, kMutTargets);
+    gather_slots(s, mg.sent, b0, b1, tc, part, mg.R);
+    const double v = gather_groups(s);
+    if (threadIdx.x >= 3 * kGatherTargets || t >= nt || (a0 == a1 && b0 == b1)) return;
+    out[(threadIdx.x >> 4) * ostride + t] += v;
 }
 
 void launch_mutual_gather(hipStream_t st, int nt, const MutualGather &mg, const double *part, double *out, long ostride)
 {
     if (nt <= 0) return;
-    hipLaunchKernelGGL(k_mutual_gather, dim3((nt + 3) / 4), dim3(256), 0, st, nt, mg, part, out, ostride);
+    hipLaunchKernelGGL(k_mutual_gather, dim3((nt + kGatherTargets - 1) / kGatherTargets), dim3(256), 0, st, nt, mg, part,
+                       out, ostride);
 }
 
 void launch_mutual(hipStream_t st, int kind, int n, const MutualWork *work, int R, const PairSrc &g, double *part)
