@@ -698,6 +698,19 @@ static void syn_run(Ctx &c, const std::vector<SynJob> &jobs, double *z0 = nullpt
     launch_synth_batch(c.stream, jobs.data(), (int)jobs.size(), z0, nz0, z1, nz1);
 }
 
+// Whether stand-alone transforms of value fields take the batched kernels (one
+// launch) rather than the matrix cores (a Legendre and a Fourier launch, the
+// latter wide enough for dozens of fields). Round trips of contexts in turn
+// and one alone, matrix cores against batched: 16 fields of degree 16 17.3 and
+// 37 us against 10.4 and 22 to 42; 24 of degree 31 17.3 and 42 against 10.4 and
+// 42; 12 of degree 63 on the 126 grid 34 and 91 against 33 and 80; but 48 of
+// degree 31 43 alone against 66, and 12 of degree 12 on the 256 grid 51.6
+// against 53.4. The mixed form keeps its FP32 operands.
+static bool few_fields(const Ctx &c, int q, int nf)
+{
+    return c.opt.precision == BIM_PREC_FP64 && nf <= 24 && q <= 128;
+}
+
 static void synth(Ctx &c, int p, int q, int nf, const double *coef, long cstride, int dt, int dp, double *out,
                   long ostride)
 {
@@ -3923,7 +3936,7 @@ int bim_sh_synthesize(bim_ctx h, int p, int q, int nf, const double *coef, int d
             cin = ci.d();
             gout = go.d();
         }
-        if (dt == 0 && dp == 0 && xform_fits(p, q, false)) {
+        if (dt == 0 && dp == 0 && xform_fits(p, q, false) && !few_fields(c, q, nf)) {
             Ctx::XPlan &pl = xfield_plan(c, p, q, nf);
             std::vector<XJob> jobs;
             size_t goff = 0;
@@ -3957,7 +3970,7 @@ int bim_sh_analyze(bim_ctx h, int q, int p, int nf, const double *grid_in, doubl
             gin = gi.d();
             cout = co.d();
         }
-        if (xform_fits(p, q, true)) {
+        if (xform_fits(p, q, true) && !few_fields(c, q, nf)) {
             Ctx::XPlan &pl = xfield_plan(c, p, q, nf);
             std::vector<XJob> jobs;
             size_t goff = 0;
