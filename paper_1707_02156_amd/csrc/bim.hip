@@ -61,8 +61,8 @@ void launch_near_interp(hipStream_t st, const NearArgs &a, int kind, const doubl
 void launch_pair(hipStream_t st, int kind, int T, int n, const PairWork *work, int item0, int tile, const int *tlist,
                  const double *tx, long tstride, const PairSrc &g0, const PairSrc &g1, double *part,
                  const float4 *rec0 = nullptr, const float4 *rec1 = nullptr, const double *cb32 = nullptr, int nd = 0);
-void launch_pair_pack32(hipStream_t st, int kind, const void *jobs, int njobs, int maxn, const PairSrc &g,
-                        const double *cb, float4 *rec);
+void launch_pair_pack32(hipStream_t st, int kind, const void *jobs, int n0, int n1, int maxn, const PairSrc &g0,
+                        const PairSrc &g1, const double *cb, float4 *rec0, float4 *rec1);
 void launch_pair_gather(hipStream_t st, int nt, int tile, const int *tile_of, const int *toff, const int *tent,
                         const int *off, const int *ent, const double *part, double *out, long ostride, bool add);
 void launch_mutual(hipStream_t st, int kind, int n, const MutualWork *work, int R, const PairSrc &g, double *part);
@@ -1816,9 +1816,8 @@ static void pack32(Ctx &c, int kind, const PairSrc &g0, const PairSrc &g1)
         c.rec32_0.ensure((size_t)std::max<long>(1, c.T) * 3 * sizeof(float4));
         c.rec32_1.ensure((size_t)std::max<long>(1, c.S1) * 3 * sizeof(float4));
     }
-    launch_pair_pack32(c.stream, kind, c.pack_jobs.as<PackJob>(), c.pack_n0, c.pack_max0, g0, c.cbnd.d(),
-                       c.rec32_0.as<float4>());
-    launch_pair_pack32(c.stream, kind, c.pack_jobs.as<PackJob>() + c.pack_n0, c.pack_n1, c.pack_max1, g1, c.cbnd.d(),
+    launch_pair_pack32(c.stream, kind, c.pack_jobs.as<PackJob>(), c.pack_n0, c.pack_n1,
+                       std::max(c.pack_max0, c.pack_max1), g0, g1, c.cbnd.d(), c.rec32_0.as<float4>(),
                        c.rec32_1.as<float4>());
 }
 

@@ -631,11 +631,16 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
 // terms,
 //   DL (x, y, z, u0) (u1, u2, wN0, wN1) (wN2, -, -, -)
 //   SL (x, y, z, wW f0) (wW f1, wW f2, -, -) (-)
-// Job b covers nodes [off, off + n) of drop `drop`.
+// Job b covers nodes [off, off + n) of drop `drop`, of the standard grid for b <
+// n0 and of the upsampled one after that: both in one launch (two of 5 us each
+// per operator application before, one of 5.4 us).
 template <int KIND>
-__global__ void k_pair_pack32(const PackJob *__restrict__ jobs, PairSrc G, const double *__restrict__ cb,
-                              float4 *__restrict__ rec)
+__global__ void k_pair_pack32(const PackJob *__restrict__ jobs, int n0, PairSrc g0, PairSrc g1,
+                              const double *__restrict__ cb, float4 *__restrict__ rec0, float4 *__restrict__ rec1)
 {
+    const bool first = (int)blockIdx.y < n0;
+    const PairSrc &G = first ? g0 : g1;
+    float4 *rec = first ? rec0 : rec1;
     const PackJob jb = jobs[blockIdx.y];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= jb.n) return;
@@ -1279,23 +1284,23 @@ void launch_pair(hipStream_t st, int kind, int T, int n, const PairWork *work, i
         go(std::integral_constant<int, 1>());
 }
 
-void launch_pair_pack32(hipStream_t st, int kind, const void *jobs, int njobs, int maxn, const PairSrc &g,
-                        const double *cb, float4 *rec)
+void launch_pair_pack32(hipStream_t st, int kind, const void *jobs, int n0, int n1, int maxn, const PairSrc &g0,
+                        const PairSrc &g1, const double *cb, float4 *rec0, float4 *rec1)
 {
-    if (njobs <= 0 || maxn <= 0) return;
-    const dim3 grid((maxn + 255) / 256, njobs);
+    if (n0 + n1 <= 0 || maxn <= 0) return;
+    const dim3 grid((maxn + 255) / 256, n0 + n1);
     if (kind == 0)
-        hipLaunchKernelGGL(k_pair_pack32<0>, grid, dim3(256), 0, st, (const PackJob *)jobs, g, cb, rec);
+        hipLaunchKernelGGL(k_pair_pack32<0>, grid, dim3(256), 0, st, (const PackJob *)jobs, n0, g0, g1, cb, rec0, rec1);
     else
-        hipLaunchKernelGGL(k_pair_pack32<1>, grid, dim3(256), 0, st, (const PackJob *)jobs, g, cb, rec);
+        hipLaunchKernelGGL(k_pair_pack32<1>, grid, dim3(256), 0, st, (const PackJob *)jobs, n0, g0, g1, cb, rec0, rec1);
 }
 
 void launch_pair_gather(hipStream_t st, int nt, int tile, const int *tile_of, const int *toff, const int *tent,
                         const int *off, const int *ent, const double *part, double *out, long ostride, bool add)
 {
     if (nt <= 0) return;
-    hipLaunchKernelGGL(k_pair_gather, dim3((nt + kGatherTargets - 1) / kGatherTargets), dim3(256), 0, st, nt, tile, tile_of, toff, tent, off, ent,
-                       part, out, ostride, add ? 1 : 0);
+    hipLaunchKernelGGL(k_pair_gather, dim3((nt + kGatherTargets - 1) / kGatherTargets), dim3(256), 0, st, nt, tile,
+                       tile_of, toff, tent, off, ent, part, out, ostride, add ? 1 : 0);
 }
 
 void launch_rhs(hipStream_t st, int T, const double *tx, long tstride, const double *s, double a, const double *U0,
