@@ -337,9 +337,9 @@ int bim_synchronize(bim_ctx ctx);
  * (pair sums), "near" (nearest-region interpolation points and
  * interpolation), "synthesis", "analysis", "classify". Each timed launch adds an
  * event pair to the stream, which delays the next launch by a few
- * microseconds; bim_profile_select limits timing to chosen kernels. While it
- * is on, "dl_apply" and the "synthesis" before it, else one launch for small
- * systems, are launched apart (same results). */
+ * microseconds; bim_profile_select limits timing to chosen kernels. While all
+ * kernels are timed, "dl_apply" and the "synthesis" before it, else one launch
+ * for small systems (counted as "dl_apply"), are launched apart: same results. */
 int bim_profile(bim_ctx ctx, int enable);
 /* Restricts event timing to the kernels named in a comma-separated list
  * (NULL or "" = all kernels). Launch counts, flops and bytes are still

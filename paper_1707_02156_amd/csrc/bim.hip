@@ -2134,7 +2134,8 @@ static void xanal_drops(Ctx &c, const double *gridv, const double *x, double *y,
 // returns whether they were (else z0, z1 have been cleared and they are left
 // to the caller).
 static bool density_nodes(Ctx &c, const double *dens, const std::vector<char> &need, bool f32, double *z0 = nullptr,
-                          long nz0 = 0, double *z1 = nullptr, long nz1 = 0, const std::vector<DlJob> *rows = nullptr)
+                          long nz0 = 0, double *z1 = nullptr, long nz1 = 0, const std::vector<DlJob> *rows = nullptr,
+                          double rows_flops = 0.0, double rows_bytes = 0.0)
 {
     bool with_rows = false;
     f32 = f32 && c.opt.precision == BIM_PREC_MIXED;
@@ -2157,6 +2158,7 @@ static bool density_nodes(Ctx &c, const double *dens, const std::vector<char> &n
             jobs.push_back(syn_job(c, d.p, d.qu, 3, dens + d.coff, c.Ctot, 0x1, c.s1d.d() + d.uoff, c.S1, 0));
         }
         if (rw && synth_rows_fits(jobs.data(), (int)jobs.size(), (int)rw->size())) {
+            ProfScope ps(c, "dl_apply", rows_flops, rows_bytes);
             launch_synth_rows(c.stream, jobs.data(), (int)jobs.size(), rw->data(), (int)rw->size(), c.Ctot, c.T);
             with_rows = true;
             return;
@@ -2473,12 +2475,12 @@ static void double_layer_grid(Ctx &c, const double *ucoef, const std::vector<dou
         }
     }
     // every self-interaction from stored rows (or absent) and into acc: in the
-    // launch of the density synthesis (two launches when launches are timed one
-    // by one); else acc (and near_self) are cleared by that launch and added to
+    // launch of the density synthesis (two launches when all kernels are timed
+    // one by one); else acc (and near_self) are cleared by that launch and added to
     const bool near = !c.near_h.empty();
-    const bool joint = stored && !near && !jobs.empty() && !c.prof_on;
+    const bool joint = stored && !near && !jobs.empty() && !(c.prof_on && c.prof_sel.empty());
     if (!density_nodes(c, ucoef, need, true, c.acc.d(), 3 * c.T, near ? c.near_self.d() : nullptr, near ? 3 * c.T : 0,
-                       joint ? &all : nullptr)) {
+                       joint ? &all : nullptr, dfl, dby)) {
         if (!jobs.empty()) {
             ProfScope ps(c, "dl_apply", dfl, dby);
             launch_dl_apply_multi(c.stream, jobs.data(), (int)jobs.size(), c.Ctot, c.T);

@@ -15,7 +15,7 @@
 //                  analysis Fa^mu[j'][target*12 + pair*2 + re/im]
 //   LA k_leg_mfma  Legendre analysis Bt^mu = (Ptilde^mu)^T Fa^mu (same kernel)
 //   AR k_adjrot_mfma adjoint rotation (matrix cores) -> rows of the stored double layer
-//                  M[t][pair][2 ncoef(p)] (applied by k_dl_apply)
+//                  M[t][pair][2 ncoef(p)] (applied by dl_row, dl_row.hpp)
 //
 // Layouts: a triangle-ordered operand stores order mu as the rows n = mu..p at
 // row offset koff(mu) = mu (p+1) - mu (mu-1)/2, each row NC doubles wide.
