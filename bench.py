@@ -64,9 +64,10 @@ WORKLOADS = {
 
 # HBM bytes per launch of a kernel from committed rocprofv3 counters
 # (FETCH_SIZE x 2.0 and WRITE_SIZE x 1.0, the factors a plain copy of known
-# size gives), valid while the kernel's source file is unchanged.
+# size gives), valid while the kernels' source files are unchanged.
 TRAFFIC = {("pair_dl", "deformed_drops"): ("profiles/pair_dl_deformed_drops_p48_counters.md",
-                                            "paper_1707_02156_amd/csrc/kernels.hip")}
+                                            "paper_1707_02156_amd/csrc/kernels.hip",
+                                            "paper_1707_02156_amd/csrc/kernels_mutual.hip")}
 
 
 def workload(name):
@@ -82,10 +83,10 @@ def traffic(kernel, wname):
     ent = TRAFFIC.get((kernel, wname))
     if not ent:
         return None
-    prof, src = (os.path.join(ROOT, x) for x in ent)
+    prof, *src = (os.path.join(ROOT, x) for x in ent)
     try:
         text = open(prof).read()
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        sha = hashlib.sha256(b"".join(open(x, "rb").read() for x in src)).hexdigest()
     except OSError:
         return None
     m = re.search(r"traffic_bytes_per_launch:\s*([0-9.eE+]+)\s+source_sha256:\s*([0-9a-f]{64})", text)
