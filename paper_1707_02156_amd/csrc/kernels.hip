@@ -849,7 +849,6 @@ __device__ inline void givens_column(int kc, double *scol, const double *scs, co
     ga.res[0] = fabs(ga.g[kc + 1]) / ga.bnorm;  // host-visible memory
     __threadfence_system();
     ga.res[1] = ga.stamp;  // the host reads the estimate once it sees this step's stamp
-    __threadfence_system();
 }
 
 template <bool UPD, bool NRM>
@@ -1000,7 +999,8 @@ __global__ __launch_bounds__(256) void k_gs(long n, int kv, const double *__rest
 // large (gs_small). Sums in a fixed order: a basis vector's product is split
 // over S wavefronts (a power of two), added in order.
 // Measured per step: n = 1836, kv 1..15: 12 us against 23 for the three
-// kernels; n = 6732: 12 us at kv = 1, 36 at kv = 17, against 26 and 33.
+// kernels; n = 6732: 12 us at kv = 1, 36 at kv = 17, against 26 and 33. Fewer
+// vectors stay in registers (k_gs_reg).
 constexpr int kGsSmallThreads = 1024, kGsSmallWaves = kGsSmallThreads / 64;
 
 __global__ __launch_bounds__(kGsSmallThreads) void k_gs_small(int n2, int kv, const double2 *__restrict__ V, long ld2,
@@ -1087,6 +1087,123 @@ __global__ __launch_bounds__(kGsSmallThreads) void k_gs_small(int n2, int kv, co
     for (int k = 0; k < kGsSmallWaves; ++k) s += snrm[k];
     const double t = sqrt(s), ti = t > 0.0 ? 1.0 / t : 0.0;  // zero norm: v = 0
     for (int e = tid; e < n2; e += kGsSmallThreads) vout[e] = make_double2(sw[e].x * ti, sw[e].y * ti);
+    if (tid == 0) {
+        scol[kv] = t;
+        givens_column(kc, scol, scs, ssn, sgk, ga);
+    }
+    __syncthreads();
+    double *col = ga.H + (long)kc * ga.ldH;  // column kc of R, rows 0..kc+1
+    if (tid <= kc + 1) col[tid] = scol[tid];
+}
+
+// Sum of v over a row of 16 lanes, in every lane (DPP rotations).
+__device__ inline double row_sum(double v)
+{
+#define ROW_ADD(ctl)                                                                                   \
+    v += __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctl, 0xf, 0xf, false),            \
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), ctl, 0xf, 0xf, false));
+    ROW_ADD(0x128)
+    ROW_ADD(0x124)
+    ROW_ADD(0x122)
+    ROW_ADD(0x121)
+#undef ROW_ADD
+    return v;
+}
+
+// The same step with w and the basis in registers, R 16-byte entries of each
+// per thread and up to K vectors: the basis is read once, all loads in flight
+// together, instead of four times. A product's partial sums are added over rows of
+// lanes, then by one wavefront per vector, in a fixed order.
+// Per step at n = 1836, kv 1..16: 8.3 us against 11.3 for k_gs_small (mean of the
+// solves of a coupled step); n = 6732, kv 1..4: 6.8 against 12 to 16.
+template <int R, int K>
+__global__ __launch_bounds__(kGsSmallThreads) void k_gs_reg(int n2, int kv, const double2 *__restrict__ V, long ld2,
+                                                            const double2 *__restrict__ w, GivensArgs ga,
+                                                            double2 *__restrict__ vout)
+{
+    static_assert(K <= kGsSmallWaves, "one wavefront per vector");
+    __shared__ double spart[K][64], sh[K], scol[K + 2], scs[K], ssn[K], sgk;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), kc = kv - 1;
+    double2 x[R], v[K][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = tid + r * kGsSmallThreads;
+        x[r] = e < n2 ? w[e] : make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = tid + r * kGsSmallThreads;
+            v[i][r] = i < kv && e < n2 ? V[i * ld2 + e] : make_double2(0.0, 0.0);
+        }
+    if (tid < kc) {
+        scs[tid] = ga.cs[tid];
+        ssn[tid] = ga.sn[tid];
+    }
+    if (tid == 0) sgk = ga.g[kc];
+    // sums over the block of one value per vector index, into sh
+    auto reduce = [&](int i, double s) {
+        s = row_sum(s);
+        if ((lane & 15) == 0) spart[i][tid >> 4] = s;
+    };
+    auto finish = [&](int n) {
+        __syncthreads();
+        if (wv < n) {
+            double s = row_sum(spart[wv][lane]);
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (lane == 0) sh[wv] = s;
+        }
+        __syncthreads();
+    };
+    for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (i < kv) {
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    s0 = fma(v[i][r].x, x[r].x, s0);
+                    s1 = fma(v[i][r].y, x[r].y, s1);
+                }
+                reduce(i, s0 + s1);
+            }
+        finish(kv);
+        if (tid < kv) scol[tid] = pass ? scol[tid] + sh[tid] : sh[tid];
+        double2 a[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[r] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (i < kv) {
+                const double h = sh[i];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    a[r].x = fma(h, v[i][r].x, a[r].x);
+                    a[r].y = fma(h, v[i][r].y, a[r].y);
+                }
+            }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            x[r].x -= a[r].x;
+            x[r].y -= a[r].y;
+        }
+    }
+    double q = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) q = fma(x[r].x, x[r].x, fma(x[r].y, x[r].y, q));
+    reduce(0, q);
+    __syncthreads();
+    double s = row_sum(spart[0][lane]);
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    const double t = sqrt(s), ti = t > 0.0 ? 1.0 / t : 0.0;  // zero norm: v = 0
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = tid + r * kGsSmallThreads;
+        if (e < n2) vout[e] = make_double2(x[r].x * ti, x[r].y * ti);
+    }
     if (tid == 0) {
         scol[kv] = t;
         givens_column(kc, scol, scs, ssn, sgk, ga);
@@ -1364,8 +1481,20 @@ bool gs_small(long n, int kv)
 void launch_gs_small(hipStream_t st, long n, int kv, const double *V, const double *w, const GivensArgs &ga,
                      double *vout)
 {
-    hipLaunchKernelGGL(k_gs_small, dim3(1), dim3(kGsSmallThreads), n * sizeof(double), st, (int)(n / 2), kv,
-                       (const double2 *)V, n / 2, (const double2 *)w, ga, (double2 *)vout);
+    auto go = [&](auto fn, size_t lds) {
+        hipLaunchKernelGGL(fn, dim3(1), dim3(kGsSmallThreads), lds, st, (int)(n / 2), kv, (const double2 *)V, n / 2,
+                           (const double2 *)w, ga, (double2 *)vout);
+    };
+    // w and the basis in registers while they fit 16 to 18 entries of 16 bytes a
+    // thread (94 to 110 VGPRs of the 128 that 1024 threads leave)
+    if (n <= 2 * kGsSmallThreads && kv <= 16)
+        go(k_gs_reg<1, 16>, 0);
+    else if (n <= 4 * kGsSmallThreads && kv <= 9)
+        go(k_gs_reg<2, 9>, 0);
+    else if (n <= 8 * kGsSmallThreads && kv <= 4)
+        go(k_gs_reg<4, 4>, 0);
+    else
+        go(k_gs_small, n * sizeof(double));
 }
 
 void launch_backsub(hipStream_t st, int k, const double *H, long ldH, const double *g, double *y)
