@@ -1512,15 +1512,15 @@ static int tune_fmm(Ctx &c, const std::vector<double> &cb0, const std::vector<do
 // choice depends on the
 // problem's shape only, so it is cached for the process under (direct pairs
 // of an application to two significant digits, targets, order of the fast
-// summation): later contexts of the same shape reuse it without timing, and
+// summation, precision): later contexts of the same shape reuse it without timing, and
 // contexts that time the same shape concurrently all adopt the first result
 // stored, so results in one process do not depend on which context tuned.
 struct PairShapeKey {
-    long mant, targets;  // pairs = mant 10^expo, mant in [10, 99]
-    int expo, P;
+    long mant, targets;  // direct pairs = mant 10^expo, mant in [10, 99]
+    int expo, P, precision;
     bool operator<(const PairShapeKey &o) const
     {
-        return std::tie(mant, expo, targets, P) < std::tie(o.mant, o.expo, o.targets, o.P);
+        return std::tie(mant, expo, targets, P, precision) < std::tie(o.mant, o.expo, o.targets, o.P, o.precision);
     }
 };
 static std::mutex g_shape_mu;
@@ -1528,8 +1528,13 @@ static std::map<PairShapeKey, std::pair<int, int>> g_shapes;
 constexpr float kTuneMargin = 0.03f;
 constexpr float kTuneLongMs = 2.0f;
 
-// Returns whether the lists are built with the shape chosen.
-static bool tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std::vector<double> &cb1)
+// Whether the partial sums of the lists just built fit the no-allocation scratch.
+static bool pairs_fit_scratch(const Ctx &c)
+{
+    return (double)(c.w0h.size() + c.w1h.size()) * 3 * 64 * c.pair_T <= (double)kScratchDoubles;
+}
+
+static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std::vector<double> &cb1)
 {
     // the lists are built with the shape used last in this context (the lookup
     // below needs their number of pairs): usually the one that is found
@@ -1537,21 +1542,33 @@ static bool tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     c.pair_ch = c.last_ch;
     build_lists(c, P, cb0, cb1);
     c.pair_tuned = true;
-    if (c.npairs_direct <= 0.0) return true;
-    double all = c.npairs_direct;
-    for (auto &ij : c.mut.pairs) all += 2.0 * npts(c.drops[ij.first].p) * npts(c.drops[ij.second].p);
-    const int expo = (int)std::floor(std::log10(all)) - 1;
-    const PairShapeKey key{(long)std::llround(all / std::pow(10.0, expo)), c.T, expo, P};
+    if (c.npairs_direct <= 0.0) return;
+    // the lists of the shape found or chosen. It may come from a problem whose
+    // pairs agree to two digits only: one whose partial sums exceed the
+    // no-allocation scratch gives way to the rule's where that fits.
+    auto use = [&](int T, int ch, bool built) {
+        c.pair_T_fix = c.last_T = T;
+        c.pair_ch = c.last_ch = ch;
+        if (!built) build_lists(c, P, cb0, cb1);
+        if (pairs_fit_scratch(c)) return;
+        c.pair_T_fix = c.pair_ch = 0;
+        build_lists(c, P, cb0, cb1);
+        if (pairs_fit_scratch(c)) return;
+        c.pair_T_fix = T;
+        c.pair_ch = ch;
+        build_lists(c, P, cb0, cb1);
+    };
+    // the direct pairs the shape is for: mutual pairs and those of the fast
+    // summation are not among them, and the precision's kernel is another
+    const int expo = (int)std::floor(std::log10(c.npairs_direct)) - 1;
+    const PairShapeKey key{(long)std::llround(c.npairs_direct / std::pow(10.0, expo)), c.T, expo, P, c.opt.precision};
+    int T = 0, ch = 0;
     {
         std::lock_guard<std::mutex> lk(g_shape_mu);
         auto it = g_shapes.find(key);
-        if (it != g_shapes.end()) {
-            const bool built = c.last_T == it->second.first && c.last_ch == it->second.second;
-            c.pair_T_fix = c.last_T = it->second.first;
-            c.pair_ch = c.last_ch = it->second.second;
-            return built;
-        }
+        if (it != g_shapes.end()) std::tie(T, ch) = it->second;
     }
+    if (T) return use(T, ch, c.last_T == T && c.last_ch == ch);
     const std::vector<double> ones((size_t)c.nd * c.nd, 1.0);
     hipEvent_t e0, e1;
     HIPC(hipEventCreate(&e0));
@@ -1576,6 +1593,7 @@ static bool tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     }
     if (std::find(cand.begin(), cand.end(), std::make_pair(rT, rch)) == cand.end()) cand.emplace_back(rT, rch);
     std::vector<float> best(cand.size(), 0.0f);
+    std::vector<char> fits(cand.size(), 1);
     TimedAcc own(c);
     // A second round evens out what varies between passes of a few tens of
     // microseconds; passes of kTuneLongMs are timed once (they repeat within 1 %),
@@ -1588,6 +1606,7 @@ static bool tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
             c.pair_T_fix = cand[k].first;
             c.pair_ch = cand[k].second;
             build_lists(c, P, cb0, cb1);
+            fits[k] = pairs_fit_scratch(c);
             (void)work_lists(c, ones);
             if (round == 0 && (longest < kTuneLongMs || cand[k].first != cand[k - 1].first))
                 run_pairs(c, 1, ones);  // warm-up
@@ -1604,14 +1623,13 @@ static bool tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     (void)hipEventDestroy(e1);
     size_t kr = std::find(cand.begin(), cand.end(), std::make_pair(rT, rch)) - cand.begin(), kb = kr;
     for (size_t k = 0; k < cand.size(); ++k)
-        if (best[k] < best[kb]) kb = k;
+        if (best[k] < best[kb] && (fits[k] || !fits[kr])) kb = k;
     if (!(best[kb] < (1.0f - kTuneMargin) * best[kr])) kb = kr;
-    const int bestT = cand[kb].first, bestch = cand[kb].second;
-    std::lock_guard<std::mutex> lk(g_shape_mu);
-    const auto it = g_shapes.emplace(key, std::make_pair(bestT, bestch)).first;  // the first stored wins
-    c.pair_T_fix = c.last_T = it->second.first;
-    c.pair_ch = c.last_ch = it->second.second;
-    return false;
+    {
+        std::lock_guard<std::mutex> lk(g_shape_mu);
+        std::tie(T, ch) = g_shapes.emplace(key, cand[kb]).first->second;  // the first stored wins
+    }
+    use(T, ch, false);
 }
 
 // The regions of every target are built in two parts: regions_begin enqueues
@@ -1702,9 +1720,10 @@ static void regions_finish(Ctx &c)
         if (c.fmm_tuned < 0) c.fmm_tuned = tune_fmm(c, cb0, cb1);
         P = c.fmm_tuned;
     }
-    bool built = false;
-    if (c.opt.pair_tune && pairs && !c.pair_tuned) built = tune_pairs(c, P, cb0, cb1);
-    if (!built) build_lists(c, P, cb0, cb1);
+    if (c.opt.pair_tune && pairs && !c.pair_tuned)
+        tune_pairs(c, P, cb0, cb1);
+    else
+        build_lists(c, P, cb0, cb1);
     near_setup(c);
     c.regions_ok = true;
 }
