@@ -121,8 +121,9 @@ typedef struct {
                             sources per item) is chosen by timing a double-layer pair pass
                             of each candidate at the first evaluation after bim_set_drops, and
                             kept for later contexts of the same problem shape (same number of
-                            directly summed pairs to two digits, targets, fast-summation order,
-                            precision) in the process; 0: a rule from the pair count. Only the speed depends on it */
+                            directly summed pairs to half a power of two, targets, fast-summation
+                            order, precision) in the process; 0: a rule from the pair count. Only
+                            the speed depends on it */
     int xform_path;      /* spherical-harmonic transforms of value fields inside the velocity
                             evaluation (density values on the nodes, Galerkin analysis; Sec. 1.1,
                             2.1): 1: scalar FMA kernels (FP64); 2: Legendre and Fourier sums as

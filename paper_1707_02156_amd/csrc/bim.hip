@@ -1509,18 +1509,21 @@ static int tune_fmm(Ctx &c, const std::vector<double> &cb0, const std::vector<do
 // passes counted. The rule's own shape is kept unless a candidate
 // beats it by more than kTuneMargin (a single pass varies by a few percent
 // run to run; a smaller gain is not worth a shape chosen on noise). The
-// choice depends on the
-// problem's shape only, so it is cached for the process under (direct pairs
-// of an application to two significant digits, targets, order of the fast
-// summation, precision): later contexts of the same shape reuse it without timing, and
-// contexts that time the same shape concurrently all adopt the first result
-// stored, so results in one process do not depend on which context tuned.
+// choice depends on the problem's shape only, so it is cached for the process
+// under (direct pairs of an application to half a power of two, targets, order
+// of the fast summation, precision): later contexts of the same shape reuse it
+// without timing, and contexts that time the same shape concurrently all adopt
+// the first result stored, so results in one process do not depend on which
+// context tuned. Candidates are a factor of two apart, and the pairs that the
+// mutual kernel leaves differ by a tenth between sets of drops of one kind (16
+// drops of degree 48: to two digits nearly every new set was timed again, 174
+// ms for its first single layer against 128).
 struct PairShapeKey {
-    long mant, targets;  // direct pairs = mant 10^expo, mant in [10, 99]
-    int expo, P, precision;
+    long bin, targets;  // direct pairs within [2^(bin / 2), 2^((bin + 1) / 2))
+    int P, precision;
     bool operator<(const PairShapeKey &o) const
     {
-        return std::tie(mant, expo, targets, P, precision) < std::tie(o.mant, o.expo, o.targets, o.P, o.precision);
+        return std::tie(bin, targets, P, precision) < std::tie(o.bin, o.targets, o.P, o.precision);
     }
 };
 static std::mutex g_shape_mu;
@@ -1543,9 +1546,9 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     build_lists(c, P, cb0, cb1);
     c.pair_tuned = true;
     if (c.npairs_direct <= 0.0) return;
-    // the lists of the shape found or chosen. It may come from a problem whose
-    // pairs agree to two digits only: one whose partial sums exceed the
-    // no-allocation scratch gives way to the rule's where that fits.
+    // the lists of the shape found or chosen. It may come from a problem of other
+    // pairs in the same bin: one whose partial sums exceed the no-allocation
+    // scratch gives way to the rule's where that fits.
     auto use = [&](int T, int ch, bool built) {
         c.pair_T_fix = c.last_T = T;
         c.pair_ch = c.last_ch = ch;
@@ -1560,8 +1563,7 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     };
     // the direct pairs the shape is for: mutual pairs and those of the fast
     // summation are not among them, and the precision's kernel is another
-    const int expo = (int)std::floor(std::log10(c.npairs_direct)) - 1;
-    const PairShapeKey key{(long)std::llround(c.npairs_direct / std::pow(10.0, expo)), c.T, expo, P, c.opt.precision};
+    const PairShapeKey key{(long)std::floor(2.0 * std::log2(c.npairs_direct)), c.T, P, c.opt.precision};
     int T = 0, ch = 0;
     {
         std::lock_guard<std::mutex> lk(g_shape_mu);
