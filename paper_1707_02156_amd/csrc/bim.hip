@@ -1451,6 +1451,7 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
 }
 
 static void run_pairs(Ctx &c, int kind, const std::vector<double> &wt);
+static void run_direct(Ctx &c, int kind, const Ctx::WList &L);
 static Ctx::WList &work_lists(Ctx &c, const std::vector<double> &wt);
 
 // Pair passes that are only timed add into an accumulator of their own: the
@@ -1504,9 +1505,9 @@ static int tune_fmm(Ctx &c, const std::vector<double> &cb0, const std::vector<do
 // Work-item shape of the pair sums chosen by timing (option pair_tune):
 // targets per lane T in {2, 4} and sources per item ch in {ch0/2, ch0,
 // 2 ch0} (ch0 the pair-count rule's choice for that T), besides the rule's own
-// shape; double-layer pair passes (unit weights, after a warm-up pass) timed
-// with HIP events on the context stream, the faster of a candidate's two
-// passes counted. The rule's own shape is kept unless a candidate
+// shape; double-layer passes over the direct pairs (unit weights, after a
+// warm-up pass) timed with HIP events on the context stream, the faster of a
+// candidate's two passes counted. The rule's own shape is kept unless a candidate
 // beats it by more than kTuneMargin (a single pass varies by a few percent
 // run to run; a smaller gain is not worth a shape chosen on noise). The
 // choice depends on the problem's shape only, so it is cached for the process
@@ -1597,30 +1598,30 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     std::vector<float> best(cand.size(), 0.0f);
     std::vector<char> fits(cand.size(), 1);
     TimedAcc own(c);
-    // A second round evens out what varies between passes of a few tens of
-    // microseconds; passes of kTuneLongMs are timed once (they repeat within 1 %),
-    // and a pass is warmed up where its kernel or its scratch size is new
-    // (candidates of one T: the most items first). Sixteen drops of degree 48:
-    // 21 passes of 9.6 ms became 9.
+    // What is timed is the direct pairs alone: mutual pairs and the fast summation
+    // are the same for every candidate. The faster of two passes evens out what
+    // varies between passes of a few tens of microseconds; passes of kTuneLongMs
+    // are timed once (they repeat within 1 %), and warmed up where their kernel or
+    // their scratch size is new (candidates of one T: the most items first).
     float longest = 0.0f;
-    for (int round = 0; round < 2 && (round == 0 || longest < kTuneLongMs); ++round)
-        for (size_t k = 0; k < cand.size(); ++k) {
-            c.pair_T_fix = cand[k].first;
-            c.pair_ch = cand[k].second;
-            build_lists(c, P, cb0, cb1);
-            fits[k] = pairs_fit_scratch(c);
-            (void)work_lists(c, ones);
-            if (round == 0 && (longest < kTuneLongMs || cand[k].first != cand[k - 1].first))
-                run_pairs(c, 1, ones);  // warm-up
+    for (size_t k = 0; k < cand.size(); ++k) {
+        c.pair_T_fix = cand[k].first;
+        c.pair_ch = cand[k].second;
+        build_lists(c, P, cb0, cb1);
+        fits[k] = pairs_fit_scratch(c);
+        const Ctx::WList &L = work_lists(c, ones);
+        if (longest < kTuneLongMs || cand[k].first != cand[k - 1].first) run_direct(c, 1, L);  // warm-up
+        for (int pass = 0; pass < 2 && (pass == 0 || longest < kTuneLongMs); ++pass) {
             HIPC(hipEventRecord(e0, c.stream));
-            run_pairs(c, 1, ones);
+            run_direct(c, 1, L);
             HIPC(hipEventRecord(e1, c.stream));
             HIPC(hipEventSynchronize(e1));
             float ms = 0.0f;
             HIPC(hipEventElapsedTime(&ms, e0, e1));
-            best[k] = round == 0 ? ms : std::min(best[k], ms);
+            best[k] = pass == 0 ? ms : std::min(best[k], ms);
             longest = std::max(longest, ms);
         }
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     size_t kr = std::find(cand.begin(), cand.end(), std::make_pair(rT, rch)) - cand.begin(), kb = kr;
@@ -1848,39 +1849,43 @@ static bool pair_sums(const Ctx &c)
     return !c.w0h.empty() || !c.w1h.empty() || !c.mut.pairs.empty() || !c.fmm.pairs.empty();
 }
 
+// The directly summed pairs of a work list, added into acc.
+static void run_direct(Ctx &c, int kind, const Ctx::WList &L)
+{
+    if (L.n == 0) return;
+    const double fpp = kind == 0 ? 29.0 : 30.0;  // flops per pair (SL / DL)
+    const PairSrc g0{c.tx.d(), c.s0N.d(), c.s0W.d(), c.s0d.d(), c.T};
+    const PairSrc g1{c.s1x.d(), c.s1N.d(), c.s1W.d(), c.s1d.d(), c.S1};
+    const bool f32 = c.opt.precision == BIM_PREC_MIXED;
+    if (f32) {  // (allocates the record buffers on first use: their addresses are taken after it)
+        ProfScope ps(c, "pair_pack", 0.0, 0.0);
+        pack32(c, kind, g0, g1);
+    }
+    const float4 *r0 = f32 ? c.rec32_0.as<float4>() : nullptr, *r1 = f32 ? c.rec32_1.as<float4>() : nullptr;
+    REQUIRE(!f32 || (r0 && r1), BIM_EDEVICE, "FP32 source records missing");
+    const int tile = 64 * c.pair_T;
+    double *part = c.part_override ? c.part_override : c.pair_part.d();
+    {
+        // whole tiles first, the remainder items after them (they fill the launch's tail)
+        ProfScope ps(c, kind == 0 ? "pair_sl" : "pair_dl", L.pairs * fpp, 0.0);
+        launch_pair(c.stream, kind, c.pair_T, L.n, L.d.as<PairWork>(), 0, tile, c.tlist.as<int>(), c.tx.d(), c.T, g0,
+                    g1, part, r0, r1, c.cbnd.d(), c.nd);
+    }
+    ProfScope ps(c, "pair_gather", 0.0, 8.0 * 3.0 * ((double)L.g.h_tent.size() * tile + L.g.h_ent.size()));
+    launch_pair_gather(c.stream, (int)c.T, tile, c.tile_of.as<int>(), L.g.toff.as<int>(), L.g.tent.as<int>(),
+                       L.g.off.as<int>(), L.g.ent.as<int>(), part, c.acc.d(), c.T, true);
+}
+
 static void run_pairs(Ctx &c, int kind, const std::vector<double> &wt)
 {
     if (!pair_sums(c)) return;
     Ctx::WList &L = work_lists(c, wt);
-    const double fpp = kind == 0 ? 29.0 : 30.0;  // flops per pair (SL / DL)
-    const PairSrc g0{c.tx.d(), c.s0N.d(), c.s0W.d(), c.s0d.d(), c.T};
-    const PairSrc g1{c.s1x.d(), c.s1N.d(), c.s1W.d(), c.s1d.d(), c.S1};
-    if (L.n > 0) {
-        const bool f32 = c.opt.precision == BIM_PREC_MIXED;
-        if (f32) {  // (allocates the record buffers on first use: their addresses are taken after it)
-            ProfScope ps(c, "pair_pack", 0.0, 0.0);
-            pack32(c, kind, g0, g1);
-        }
-        const float4 *r0 = f32 ? c.rec32_0.as<float4>() : nullptr, *r1 = f32 ? c.rec32_1.as<float4>() : nullptr;
-        REQUIRE(!f32 || (r0 && r1), BIM_EDEVICE, "FP32 source records missing");
-        const int tile = 64 * c.pair_T;
-        double *part = c.part_override ? c.part_override : c.pair_part.d();
-        {
-            // whole tiles first, the remainder items after them (they fill the launch's tail)
-            ProfScope ps(c, kind == 0 ? "pair_sl" : "pair_dl", L.pairs * fpp, 0.0);
-            launch_pair(c.stream, kind, c.pair_T, L.n, L.d.as<PairWork>(), 0, tile, c.tlist.as<int>(), c.tx.d(), c.T,
-                        g0, g1, part, r0, r1, c.cbnd.d(), c.nd);
-        }
-        {
-            ProfScope ps(c, "pair_gather", 0.0, 8.0 * 3.0 * ((double)L.g.h_tent.size() * tile + L.g.h_ent.size()));
-            launch_pair_gather(c.stream, (int)c.T, tile, c.tile_of.as<int>(), L.g.toff.as<int>(), L.g.tent.as<int>(),
-                               L.g.off.as<int>(), L.g.ent.as<int>(), part, c.acc.d(), c.T, true);
-        }
-    }
+    run_direct(c, kind, L);
     if (L.nmut > 0) {  // its partial sums reuse the buffer, in stream order
         double *part = c.part_override ? c.part_override : c.pair_part.d();
         {
-            ProfScope ps(c, kind == 0 ? "pair_sl" : "pair_dl", L.mpairs * fpp, 0.0);
+            const PairSrc g0{c.tx.d(), c.s0N.d(), c.s0W.d(), c.s0d.d(), c.T};
+            ProfScope ps(c, kind == 0 ? "pair_sl" : "pair_dl", L.mpairs * (kind == 0 ? 29.0 : 30.0), 0.0);
             launch_mutual(c.stream, kind, L.nmut, L.mut.as<MutualWork>(), c.mut.R, g0, part);
         }
         ProfScope ps(c, "pair_gather", 0.0, 8.0 * 3.0 * (double)L.nmut * (kMutTargets + c.mut.R));

@@ -58,3 +58,21 @@ def test_shape_of_one_precision_is_not_taken_for_the_other(B, drops):
     B.bim_synchronize(c.h)
     assert np.array_equal(out.cpu().numpy(), want)
     c.close()
+
+
+def test_only_the_direct_pairs_are_timed(B, drops):
+    """The timed passes leave out what no candidate changes: all of them together
+    (double layers; the call itself is a single layer) count fewer pairs than one
+    pass over the mutual ones (41e6 direct pairs, 21 passes at most, 1.7e9)."""
+    keep = [0] + list(range(2, ND))  # a drop less, the close pair in: a shape that is not stored yet
+    xs, fs = ([v[k] for k in keep] for v in drops)
+    nd = len(keep)
+    c = B.Context(**OPTS)
+    c.set_drops([P] * nd, xs, [2.0] * nd)
+    B.bim_profile(c.h, 1)
+    c.single_layer(fs)
+    timed = B.bim_profile_query(c.h, "pair_dl")
+    c.close()
+    mutual = (nd * (nd - 1) / 2 - 1) * 2.0 * B.npts(P) ** 2
+    assert timed["launches"] > 0
+    assert timed["flops"] < 30.0 * mutual, (timed, 30.0 * mutual)
