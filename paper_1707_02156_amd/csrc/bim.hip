@@ -176,9 +176,11 @@ struct Error {
 #define HIPC(expr)                                                                                 \
     do {                                                                                           \
         hipError_t e_ = (expr);                                                                    \
-        if (e_ != hipSuccess)                                                                      \
+        if (e_ != hipSuccess) {                                                                    \
+            (void)hipGetLastError(); /* reported here: a later launch check must not find it */    \
             throw Error{e_ == hipErrorOutOfMemory ? BIM_ENOMEM : BIM_EDEVICE,                      \
                         std::string(#expr) + ": " + hipGetErrorString(e_)};                         \
+        }                                                                                          \
     } while (0)
 
 #define REQUIRE(cond, code, msg) \
@@ -250,7 +252,10 @@ template <class T> struct PinnedAlloc {
     T *allocate(size_t n)
     {
         void *p = nullptr;
-        if (hipHostMalloc(&p, std::max<size_t>(1, n) * sizeof(T)) != hipSuccess) throw std::bad_alloc();
+        if (hipHostMalloc(&p, std::max<size_t>(1, n) * sizeof(T)) != hipSuccess) {
+            (void)hipGetLastError();
+            throw std::bad_alloc();
+        }
         return static_cast<T *>(p);
     }
     void deallocate(T *p, size_t) { (void)hipHostFree(p); }
@@ -3075,6 +3080,19 @@ int bim_set_drops(bim_ctx h, int n_drops, const int *p, const double *xcoef, con
         // the pinned images are refilled: their last uploads are over
         if (c.upload_pending) HIPC(hipStreamSynchronize(c.stream));
         c.upload_pending = false;
+        // from here on the last drops are gone: a call that fails below (an
+        // allocation) leaves a context with no drops, not new sizes on old tables
+        struct Unset {
+            Ctx *c;
+            ~Unset()
+            {
+                if (!c) return;
+                c->nd = 0;
+                c->drops.clear();
+                c->sys_up.clear();
+                invalidate(*c);
+            }
+        } unset{&c};
         c.nd = n_drops;
         c.drops = ds;
         c.xplans.clear();
@@ -3128,6 +3146,7 @@ int bim_set_drops(bim_ctx h, int n_drops, const int *p, const double *xcoef, con
             HIPC(hipMemsetAsync(c.gU.ptr, 0, 9 * sizeof(double), c.stream));
         }
         degree_tables(c);
+        unset.c = nullptr;
         return BIM_OK;
     });
 }
@@ -3139,6 +3158,7 @@ int bim_set_systems(bim_ctx h, const int *system_of_drop)
         require_drops(c);
         REQUIRE(system_of_drop, BIM_EINVAL, "null system array");
         for (int i = 0; i < c.nd; ++i) REQUIRE(system_of_drop[i] >= 0, BIM_EINVAL, "negative system id");
+        c.sys_up.clear();
         c.sys_h.assign(system_of_drop, system_of_drop + c.nd);
         HIPC(hipMemcpyAsync(c.sysd.ptr, c.sys_h.data(), c.nd * sizeof(int), hipMemcpyHostToDevice, c.stream));
         HIPC(hipStreamSynchronize(c.stream));
