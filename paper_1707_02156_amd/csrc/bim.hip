@@ -1742,6 +1742,12 @@ static void build_regions(Ctx &c)
     regions_finish(c);
 }
 
+// Whether there are pair sums other than the nearest-region items'.
+static bool pair_sums(const Ctx &c)
+{
+    return !c.w0h.empty() || !c.w1h.empty() || !c.mut.pairs.empty() || !c.fmm.pairs.empty();
+}
+
 // Device work lists for a weight table wt[i * nd + j] (items of zero weight
 // dropped), cached per table.
 static Ctx::WList &work_lists(Ctx &c, const std::vector<double> &wt)
@@ -1761,6 +1767,10 @@ static Ctx::WList &work_lists(Ctx &c, const std::vector<double> &wt)
     e->stale = false;
     e->wt = wt;
     e->pairs = 0.0;
+    if (!pair_sums(c) && c.near_h.empty()) {  // nothing to list: the entry says that the table was applied
+        e->n = e->nmut = 0;
+        return *e;
+    }
     HVec<PairWork> &keep = e->h_items;
     keep.clear();
     keep.reserve(c.w0h.size() + c.w1h.size());
@@ -1848,12 +1858,6 @@ static void pack32(Ctx &c, int kind, const PairSrc &g0, const PairSrc &g1)
                        c.rec32_1.as<float4>());
 }
 
-// Whether there are pair sums other than the nearest-region items'.
-static bool pair_sums(const Ctx &c)
-{
-    return !c.w0h.empty() || !c.w1h.empty() || !c.mut.pairs.empty() || !c.fmm.pairs.empty();
-}
-
 // The directly summed pairs of a work list, added into acc.
 static void run_direct(Ctx &c, int kind, const Ctx::WList &L)
 {
@@ -1883,7 +1887,6 @@ static void run_direct(Ctx &c, int kind, const Ctx::WList &L)
 
 static void run_pairs(Ctx &c, int kind, const std::vector<double> &wt)
 {
-    if (!pair_sums(c)) return;
     Ctx::WList &L = work_lists(c, wt);
     run_direct(c, kind, L);
     if (L.nmut > 0) {  // its partial sums reuse the buffer, in stream order
@@ -2570,7 +2573,7 @@ static void single_layer_grid(Ctx &c, const double *fcoef, const std::vector<cha
         HIPC(hipMemcpyAsync(c.near_self.ptr, c.acc.ptr, 3 * c.T * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
     run_pairs(c, 0, wt);
     run_near(c, 0, fcoef, wt);
-    if (wt_dl && (pair_sums(c) || !c.near_h.empty())) (void)work_lists(c, *wt_dl);
+    if (wt_dl) (void)work_lists(c, *wt_dl);
 }
 
 // analysis of grid vectors [3][T] into coefficients [3][Ctot]
@@ -3754,9 +3757,8 @@ int bim_apply_double_layer_noalloc(bim_ctx h, const double *u_coef, double *out,
         const Ctx::WList *L = nullptr;
         for (auto &e : c.wlists)
             if (!e->stale && e->wt == wt) L = e.get();
-        REQUIRE(L || !(pair_sums(c) || !c.near_h.empty()), BIM_ESTATE,
-                "the pair work list of this mode is not built: apply bim_apply_double_layer once first");
-        const double need = std::max(L ? (double)L->n * 3 * 64 * c.pair_T : 0.0, (double)c.near_nwork * 3 * 64);
+        REQUIRE(L, BIM_ESTATE, "the pair work list of this mode is not built: apply bim_apply_double_layer once first");
+        const double need = std::max((double)L->n * 3 * 64 * c.pair_T, (double)c.near_nwork * 3 * 64);
         REQUIRE(need <= (double)kScratchDoubles, BIM_ENOMEM,
                 "the pair partial sums need " + std::to_string((long)(need * 8 / (1 << 20))) +
                     " MiB, above the " + std::to_string((long)(kScratchDoubles * 8 >> 20)) + " MiB scratch");
