@@ -321,7 +321,8 @@ int bim_reparametrize(bim_ctx ctx, int U_rep, double P_cut, double eps, int imax
  * p <= q. Pointers are device pointers when mem_kind = 1. Value fields with
  * p <= 63 (analysis: q <= 63) run on the matrix cores, with FP32 operands and
  * accumulation in a mixed-precision context (in an FP64 one: more than 24
- * fields or q > 128); the rest on the scalar FP64 kernels. */
+ * fields, and fewer on large grids: more than 17 of degree 63 with q = 126, more
+ * than 12 of degree 61 with q = 128); the rest on the scalar FP64 kernels. */
 int bim_sh_synthesize(bim_ctx ctx, int p, int q, int nf, const double *coef, int dt, int dp,
                       double *grid, int mem_kind);
 int bim_sh_analyze(bim_ctx ctx, int q, int p, int nf, const double *grid, double *coef, int mem_kind);

@@ -705,15 +705,22 @@ static void syn_run(Ctx &c, const std::vector<SynJob> &jobs, double *z0 = nullpt
 
 // Whether stand-alone transforms of value fields take the batched kernels (one
 // launch) rather than the matrix cores (a Legendre and a Fourier launch, the
-// latter wide enough for dozens of fields). Round trips of contexts in turn
-// and one alone, matrix cores against batched: 16 fields of degree 16 17.3 and
-// 37 us against 10.4 and 22 to 42; 24 of degree 31 17.3 and 42 against 10.4 and
-// 42; 12 of degree 63 on the 126 grid 34 and 91 against 33 and 80; but 48 of
-// degree 31 43 alone against 66, and 12 of degree 12 on the 256 grid 51.6
-// against 53.4. The mixed form keeps its FP32 operands.
-static bool few_fields(const Ctx &c, int q, int nf)
+// latter wide enough for dozens of fields). Syntheses of three contexts in turn
+// and of one alone, matrix cores against batched, us: 16 fields of degree 16 8.5
+// and 23 against 5.1 and 16; 24 of degree 31 8.8 and 26 against 5.3 and 17; 12 of
+// degree 63 on the 126 grid 13.0 and 37 against 9.2 and 25. The batched form's
+// time grows with its blocks (a field, a latitude pair, 64 longitudes), the
+// other's hardly: with three blocks a CU (LDS: degrees to 61) 12 fields of degree
+// 30 on the 128 grid, 1560 blocks, 7.1 to 8.2 against 6.6, but 16, 2080 blocks,
+// 7.6 against 8.4; with two 17 of degree 63 on the 126 grid, 1088, 14.0 against
+// 12.7, but 24 of degree 62 on the 94 grid, 1152, 12.5 against 13.5. 48 fields of
+// degree 31 take 43 alone against 66. Analyses (grids to 63) stay below these counts: 24
+// fields of degree 63 13.0 and 40 against 12.9 and 34. The mixed form keeps its
+// FP32 operands.
+static bool few_fields(const Ctx &c, int p, int q, int nf)
 {
-    return c.opt.precision == BIM_PREC_FP64 && nf <= 24 && q <= 128;
+    const long blocks = (long)nf * (q / 2 + 1) * ((q / 2 + 1 + 63) / 64);
+    return c.opt.precision == BIM_PREC_FP64 && nf <= 24 && blocks <= (p <= 61 ? 1600 : 1110);
 }
 
 static void synth(Ctx &c, int p, int q, int nf, const double *coef, long cstride, int dt, int dp, double *out,
@@ -3985,7 +3992,7 @@ int bim_sh_synthesize(bim_ctx h, int p, int q, int nf, const double *coef, int d
             cin = ci.d();
             gout = go.d();
         }
-        if (dt == 0 && dp == 0 && xform_fits(p, q, false) && !few_fields(c, q, nf)) {
+        if (dt == 0 && dp == 0 && xform_fits(p, q, false) && !few_fields(c, p, q, nf)) {
             Ctx::XPlan &pl = xfield_plan(c, p, q, nf);
             std::vector<XJob> jobs;
             size_t goff = 0;
@@ -4019,7 +4026,7 @@ int bim_sh_analyze(bim_ctx h, int q, int p, int nf, const double *grid_in, doubl
             gin = gi.d();
             cout = co.d();
         }
-        if (xform_fits(p, q, true) && !few_fields(c, q, nf)) {
+        if (xform_fits(p, q, true) && !few_fields(c, p, q, nf)) {
             Ctx::XPlan &pl = xfield_plan(c, p, q, nf);
             std::vector<XJob> jobs;
             size_t goff = 0;
