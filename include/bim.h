@@ -336,8 +336,9 @@ int bim_synchronize(bim_ctx ctx);
  * "pipe_adjrot" (batched singular pipeline), "sing_fused" (fused singular
  * rule), "sing_rotate" and "sing_v1" (per-application singular path),
  * "dl_apply" (stored double layer times a density), "pair_sl", "pair_dl"
- * (pair sums), "near" (nearest-region interpolation points and
- * interpolation), "synthesis", "analysis", "classify". Each timed launch adds an
+ * (pair sums), "pair_mutual" (those of them that take both directions of a
+ * drop pair at once: counted again, not timed), "near" (nearest-region
+ * interpolation points and interpolation), "synthesis", "analysis", "classify". Each timed launch adds an
  * event pair to the stream, which delays the next launch by a few
  * microseconds; bim_profile_select limits timing to chosen kernels. While all
  * kernels are timed, "dl_apply" and the "synthesis" before it, else one launch

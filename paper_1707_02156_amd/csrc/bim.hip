@@ -1903,6 +1903,11 @@ static void run_pairs(Ctx &c, int kind, const std::vector<double> &wt)
             ProfScope ps(c, kind == 0 ? "pair_sl" : "pair_dl", L.mpairs * (kind == 0 ? 29.0 : 30.0), 0.0);
             launch_mutual(c.stream, kind, L.nmut, L.mut.as<MutualWork>(), c.mut.R, g0, part);
         }
+        if (c.prof_on) {  // counted again by themselves
+            Ctx::ProfEntry &e = c.prof["pair_mutual"];
+            ++e.launches;
+            e.flops += L.mpairs * (kind == 0 ? 29.0 : 30.0);
+        }
         ProfScope ps(c, "pair_gather", 0.0, 8.0 * 3.0 * (double)L.nmut * (kMutTargets + c.mut.R));
         launch_mutual_gather(c.stream, (int)c.T,
                              MutualGather{c.mut.dtb.as<int>(), L.moff[0].as<int>(), L.ment[0].as<int>(),
