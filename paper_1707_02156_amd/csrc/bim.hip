@@ -1028,8 +1028,9 @@ static void target_tiles(Ctx &c, int T)
         }
     }
     if (tile_of == c.tile_of_h) return;  // the same degrees and tiles as before
+    c.tile_of_h.clear();                 // (not there if the allocation fails)
+    c.tile_of.ensure(tile_of.size() * sizeof(int));
     c.tile_of_h = std::move(tile_of);
-    c.tile_of.ensure(c.tile_of_h.size() * sizeof(int));
     HIPC(hipMemcpyAsync(c.tile_of.ptr, c.tile_of_h.data(), c.tile_of_h.size() * sizeof(int), hipMemcpyHostToDevice,
                         c.stream));
 }
@@ -1229,8 +1230,9 @@ template <class F> static void mutual_plan(Ctx &c, F &&mutual)
     for (auto &pr : M.pairs) M.items += (long)M.blk[pr.first].size() * M.run[pr.second].size();
     auto up = [&](DBuf &d, std::vector<int> &h, std::vector<int> &now) {
         if (h == now) return;  // the same degrees and runs as before
+        h.clear();             // (not there if the allocation fails)
+        d.ensure(now.size() * sizeof(int));
         h = std::move(now);
-        d.ensure(h.size() * sizeof(int));
         HIPC(hipMemcpyAsync(d.ptr, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice, c.stream));
     };
     up(M.dtb, M.tb, tb);
@@ -1771,11 +1773,12 @@ static Ctx::WList &work_lists(Ctx &c, const std::vector<double> &wt)
         c.wlists.push_back(std::make_unique<Ctx::WList>());
         e = c.wlists.back().get();
     }
-    e->stale = false;
+    e->stale = true;  // until all of it is there: a step that fails leaves no list
     e->wt = wt;
     e->pairs = 0.0;
     if (!pair_sums(c) && c.near_h.empty()) {  // nothing to list: the entry says that the table was applied
         e->n = e->nmut = 0;
+        e->stale = false;
         return *e;
     }
     HVec<PairWork> &keep = e->h_items;
@@ -1812,6 +1815,7 @@ static Ctx::WList &work_lists(Ctx &c, const std::vector<double> &wt)
         e->fp.ensure(fp.size() * sizeof(FmmPair));
         HIPC(hipMemcpyAsync(e->fp.ptr, fp.data(), fp.size() * sizeof(FmmPair), hipMemcpyHostToDevice, c.stream));
     }
+    e->stale = false;
     return *e;
 }
 
