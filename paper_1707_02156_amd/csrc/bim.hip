@@ -1849,7 +1849,10 @@ static void run_fmm(Ctx &c, int kind, Ctx::WList &L)
 // relative to its centre), from the current densities.
 static void pack32(Ctx &c, int kind, const PairSrc &g0, const PairSrc &g1)
 {
-    if (c.pack_h.empty()) {
+    if (c.pack_h.empty()) {  // (filled once the buffers are there)
+        c.pack_jobs.ensure(2 * (size_t)c.nd * sizeof(PackJob));
+        c.rec32_0.ensure((size_t)std::max<long>(1, c.T) * 3 * sizeof(float4));
+        c.rec32_1.ensure((size_t)std::max<long>(1, c.S1) * 3 * sizeof(float4));
         for (int g = 0; g < 2; ++g)
             for (int j = 0; j < c.nd; ++j) {
                 const Drop &d = c.drops[j];
@@ -1858,11 +1861,8 @@ static void pack32(Ctx &c, int kind, const PairSrc &g0, const PairSrc &g1)
                 (g == 0 ? c.pack_max0 : c.pack_max1) = std::max(g == 0 ? c.pack_max0 : c.pack_max1, n);
             }
         c.pack_n0 = c.pack_n1 = c.nd;
-        c.pack_jobs.ensure(c.pack_h.size() * sizeof(PackJob));
         HIPC(hipMemcpyAsync(c.pack_jobs.ptr, c.pack_h.data(), c.pack_h.size() * sizeof(PackJob),
                             hipMemcpyHostToDevice, c.stream));
-        c.rec32_0.ensure((size_t)std::max<long>(1, c.T) * 3 * sizeof(float4));
-        c.rec32_1.ensure((size_t)std::max<long>(1, c.S1) * 3 * sizeof(float4));
     }
     launch_pair_pack32(c.stream, kind, c.pack_jobs.as<PackJob>(), c.pack_n0, c.pack_n1,
                        std::max(c.pack_max0, c.pack_max1), g0, g1, c.cbnd.d(), c.rec32_0.as<float4>(),
@@ -2003,14 +2003,15 @@ static void xplan_upload(Ctx &c, Ctx::XPlan &pl)
 static std::vector<std::unique_ptr<Ctx::XPlan>> &xplans(Ctx &c)
 {
     if (!c.xplans.empty()) return c.xplans;
+    std::vector<std::unique_ptr<Ctx::XPlan>> plans;
     for (int i = 0; i < c.nd; ++i) {
         const Drop &d = c.drops[i];
         Ctx::XPlan *pl = nullptr;
-        for (auto &e : c.xplans)
+        for (auto &e : plans)
             if (e->p == d.p && e->qu == d.qu) pl = e.get();
         if (!pl) {
-            c.xplans.push_back(std::make_unique<Ctx::XPlan>());
-            pl = c.xplans.back().get();
+            plans.push_back(std::make_unique<Ctx::XPlan>());
+            pl = plans.back().get();
             pl->p = d.p;
             pl->qu = d.qu;
         }
@@ -2023,7 +2024,8 @@ static std::vector<std::unique_ptr<Ctx::XPlan>> &xplans(Ctx &c)
             ++pl->nf;
         }
     }
-    for (auto &e : c.xplans) xplan_upload(c, *e);
+    for (auto &e : plans) xplan_upload(c, *e);
+    c.xplans = std::move(plans);
     return c.xplans;
 }
 
@@ -2031,9 +2033,9 @@ static std::vector<std::unique_ptr<Ctx::XPlan>> &xplans(Ctx &c)
 // coefficient blocks of 2 ncoef(p) doubles and grids of N(q) values.
 static Ctx::XPlan &xfield_plan(Ctx &c, int p, int q, int nf)
 {
-    auto &e = c.xfields[std::make_tuple(p, q, nf)];
-    if (e) return *e;
-    e = std::make_unique<Ctx::XPlan>();
+    auto &plan = c.xfields[std::make_tuple(p, q, nf)];
+    if (plan) return *plan;
+    auto e = std::make_unique<Ctx::XPlan>();
     e->p = p;
     e->qu = q;
     e->nf = nf;
@@ -2043,7 +2045,8 @@ static Ctx::XPlan &xfield_plan(Ctx &c, int p, int q, int nf)
         e->h_gb0.push_back((long)f * npts(q));
     }
     xplan_upload(c, *e);
-    return *e;
+    plan = std::move(e);
+    return *plan;
 }
 
 static bool xform_drops_ok(const Ctx &c, bool analysis)
