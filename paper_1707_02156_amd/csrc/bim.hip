@@ -1526,13 +1526,14 @@ static int tune_fmm(Ctx &c, const std::vector<double> &cb0, const std::vector<do
 // run to run; a smaller gain is not worth a shape chosen on noise). The
 // choice depends on the problem's shape only, so it is cached for the process
 // under (direct pairs of an application to half a power of two, targets, order
-// of the fast summation, precision): later contexts of the same shape reuse it
-// without timing, and contexts that time the same shape concurrently all adopt
-// the first result stored, so results in one process do not depend on which
-// context tuned. Candidates are a factor of two apart, and the pairs that the
-// mutual kernel leaves differ by a tenth between sets of drops of one kind (16
-// drops of degree 48: to two digits nearly every new set was timed again, 174
-// ms for its first single layer against 128).
+// of the fast summation, precision), and a bin next to one that was timed takes
+// its shape: later contexts of the same shape reuse it without timing, and
+// contexts that time the same shape concurrently all adopt the first result
+// stored, so results in one process do not depend on which context tuned.
+// Candidates are a factor of two apart, and the pairs that the mutual kernel
+// leaves differ by a tenth or two between sets of drops of one kind (to two
+// digits, nearly every new set of 16 drops of degree 48 was timed again, 174 ms
+// for its first single layer against 128).
 struct PairShapeKey {
     long bin, targets;  // direct pairs within [2^(bin / 2), 2^((bin + 1) / 2))
     int P, precision;
@@ -1542,7 +1543,11 @@ struct PairShapeKey {
     }
 };
 static std::mutex g_shape_mu;
-static std::map<PairShapeKey, std::pair<int, int>> g_shapes;
+struct PairShape {
+    int T, ch;
+    bool timed;  // on these pairs, not taken from the next bin
+};
+static std::map<PairShapeKey, PairShape> g_shapes;
 constexpr float kTuneMargin = 0.03f;
 constexpr float kTuneLongMs = 2.0f;
 
@@ -1579,13 +1584,21 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     // the direct pairs the shape is for: mutual pairs and those of the fast
     // summation are not among them, and the precision's kernel is another
     const PairShapeKey key{(long)std::floor(2.0 * std::log2(c.npairs_direct)), c.T, P, c.opt.precision};
-    int T = 0, ch = 0;
+    PairShape shape{};
     {
         std::lock_guard<std::mutex> lk(g_shape_mu);
-        auto it = g_shapes.find(key);
-        if (it != g_shapes.end()) std::tie(T, ch) = it->second;
+        for (int d : {0, -1, 1}) {
+            PairShapeKey k = key;
+            k.bin += d;
+            auto it = g_shapes.find(k);
+            if (it == g_shapes.end() || (d != 0 && !it->second.timed)) continue;
+            shape = it->second;
+            shape.timed = d == 0 && shape.timed;
+            break;
+        }
+        if (shape.T) g_shapes.emplace(key, shape);
     }
-    if (T) return use(T, ch, c.last_T == T && c.last_ch == ch);
+    if (shape.T) return use(shape.T, shape.ch, c.last_T == shape.T && c.last_ch == shape.ch);
     const std::vector<double> ones((size_t)c.nd * c.nd, 1.0);
     hipEvent_t e0, e1;
     HIPC(hipEventCreate(&e0));
@@ -1644,9 +1657,10 @@ static void tune_pairs(Ctx &c, int P, const std::vector<double> &cb0, const std:
     if (!(best[kb] < (1.0f - kTuneMargin) * best[kr])) kb = kr;
     {
         std::lock_guard<std::mutex> lk(g_shape_mu);
-        std::tie(T, ch) = g_shapes.emplace(key, cand[kb]).first->second;  // the first stored wins
+        // the first stored wins
+        shape = g_shapes.emplace(key, PairShape{cand[kb].first, cand[kb].second, true}).first->second;
     }
-    use(T, ch, false);
+    use(shape.T, shape.ch, false);
 }
 
 // The regions of every target are built in two parts: regions_begin enqueues
