@@ -373,9 +373,10 @@ struct Ctx {
         HVec<PairWork> h_items;
         HVec<double> h_nw;
         HVec<FmmPair> h_fp;
-        HVec<MutualWork> h_mut;
-        HVec<int> h_moff[2], h_ment[2];  // slots of the mutual items: per block of targets, per run of sources
-        DBuf mut, moff[2], ment[2];
+        // mutual items and their slots (per block of targets, per run of sources):
+        // one pinned image and one device buffer, the others parts of it
+        HVec<char> h_mut;
+        DBuf mutual, mut, moff[2], ment[2];
         int nmut = 0;
         double mpairs = 0.0;             // target-source pairs of the mutual items per application
         DBuf d;
@@ -1247,43 +1248,46 @@ static void mutual_list(Ctx &c, const std::vector<double> &wt, Ctx::WList &e)
     e.mpairs = 0.0;
     if (M.pairs.empty()) return;
     const size_t stride = 3 * (size_t)(kMutTargets + M.R);
-    HVec<MutualWork> &w = e.h_mut;
-    w.clear();
-    w.reserve(M.items);
-    for (int k = 0; k < 2; ++k) e.h_moff[k].assign((k == 0 ? M.nblk : M.nrun) + 1, 0);
+    const size_t ncell[2] = {(size_t)M.nblk + 1, (size_t)M.nrun + 1}, nw = (size_t)M.items * sizeof(MutualWork);
+    const size_t total = nw + (ncell[0] + ncell[1] + 2 * (size_t)M.items) * sizeof(int);
+    e.h_mut.assign(total, 0);
+    MutualWork *w = reinterpret_cast<MutualWork *>(e.h_mut.data());
+    int *off[2], *ent[2];
+    off[0] = reinterpret_cast<int *>(e.h_mut.data() + nw);
+    off[1] = off[0] + ncell[0];
+    ent[0] = off[1] + ncell[1];
+    ent[1] = ent[0] + M.items;
     for (auto &pr : M.pairs) {
         const int i = pr.first, j = pr.second;
-        for (size_t a = 0; a < M.blk[i].size(); ++a) e.h_moff[0][M.blk0[i] + a + 1] += (int)M.run[j].size();
-        for (size_t b = 0; b < M.run[j].size(); ++b) e.h_moff[1][M.run0[j] + b + 1] += (int)M.blk[i].size();
-    }
-    for (int k = 0; k < 2; ++k) {
-        for (size_t q = 1; q < e.h_moff[k].size(); ++q) e.h_moff[k][q] += e.h_moff[k][q - 1];
-        e.h_ment[k].resize(M.items);
+        for (size_t a = 0; a < M.blk[i].size(); ++a) off[0][M.blk0[i] + a + 1] += (int)M.run[j].size();
+        for (size_t b = 0; b < M.run[j].size(); ++b) off[1][M.run0[j] + b + 1] += (int)M.blk[i].size();
     }
     std::vector<int> pos[2];
-    for (int k = 0; k < 2; ++k) pos[k].assign(e.h_moff[k].begin(), e.h_moff[k].end() - 1);
+    for (int k = 0; k < 2; ++k) {
+        for (size_t q = 1; q < ncell[k]; ++q) off[k][q] += off[k][q - 1];
+        pos[k].assign(off[k], off[k] + ncell[k] - 1);
+    }
     for (auto &pr : M.pairs) {
         const int i = pr.first, j = pr.second;
         for (size_t a = 0; a < M.blk[i].size(); ++a)
             for (size_t b = 0; b < M.run[j].size(); ++b) {
                 const auto &tb = M.blk[i][a], &sr = M.run[j][b];
-                const int base = (int)(w.size() * stride);  // (the scratch's size bounds it)
-                e.h_ment[0][pos[0][M.blk0[i] + a]++] = base - tb.first;
-                e.h_ment[1][pos[1][M.run0[j] + b]++] = base + 3 * kMutTargets - sr.first;
-                w.push_back(MutualWork{tb.first, tb.second, sr.first, sr.second, wt[(size_t)i * c.nd + j],
-                                       wt[(size_t)j * c.nd + i]});
+                const int base = (int)(e.nmut * stride);  // (the scratch's size bounds it)
+                ent[0][pos[0][M.blk0[i] + a]++] = base - tb.first;
+                ent[1][pos[1][M.run0[j] + b]++] = base + 3 * kMutTargets - sr.first;
+                w[e.nmut++] = MutualWork{tb.first, tb.second, sr.first, sr.second, wt[(size_t)i * c.nd + j],
+                                         wt[(size_t)j * c.nd + i]};
                 e.mpairs += 2.0 * tb.second * sr.second;
             }
     }
-    e.nmut = (int)w.size();
-    auto up = [&](DBuf &d, const auto &h) {
-        d.ensure(h.size() * sizeof(h[0]));
-        HIPC(hipMemcpyAsync(d.ptr, h.data(), h.size() * sizeof(h[0]), hipMemcpyHostToDevice, c.stream));
-    };
-    up(e.mut, w);
+    e.mutual.ensure(total);
+    HIPC(hipMemcpyAsync(e.mutual.ptr, e.h_mut.data(), total, hipMemcpyHostToDevice, c.stream));
+    char *d = e.mutual.as<char>();
+    auto part = [&](DBuf &p, const void *h, size_t bytes) { p.part_of(d + ((const char *)h - e.h_mut.data()), bytes); };
+    part(e.mut, w, nw);
     for (int k = 0; k < 2; ++k) {
-        up(e.moff[k], e.h_moff[k]);
-        up(e.ment[k], e.h_ment[k]);
+        part(e.moff[k], off[k], ncell[k] * sizeof(int));
+        part(e.ment[k], ent[k], (size_t)M.items * sizeof(int));
     }
     c.pair_part.ensure((size_t)M.items * stride * sizeof(double));
 }
@@ -1335,12 +1339,7 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
     std::map<int, int> tslot;
     // work lists: for each (target drop i, source drop j != i): Omega_0 targets
     // against j's standard grid, Omega_1/2 targets against j's upsampled grid
-    // the list's pinned image is refilled: its last upload is over
-    if (c.lists_pending) HIPC(hipStreamSynchronize(c.stream));
-    c.lists_pending = false;
-    HVec<int> &tl = c.tlist_h;
-    tl.clear();
-    std::vector<int> k0, k1;
+    std::vector<int> tl, k0, k1;
     std::vector<PairWork> w0, w1;
     std::vector<NearItem> near;
     // (target set, source range) segments, split into work items once the
@@ -1452,9 +1451,14 @@ static void build_lists(Ctx &c, int P, const std::vector<double> &cb0, const std
     target_tiles(c, c.pair_T);
     for (const Seg &g : segs)
         pair_items(g.grid == 0 ? w0 : w1, g.tl_off, g.cnt, g.contig, g.soff, g.ns, g.pair, g.grid, c.pair_T, CH, 0.0);
+    // the list's pinned image is refilled (in one piece: growing pinned memory
+    // entry by entry took 1.5 ms of a new context's first pass): its last upload is over
+    if (c.lists_pending) HIPC(hipStreamSynchronize(c.stream));
+    c.lists_pending = false;
+    c.tlist_h.assign(tl.begin(), tl.end());
     c.tlist.ensure(std::max<size_t>(1, tl.size()) * sizeof(int));
     if (!tl.empty()) {
-        HIPC(hipMemcpyAsync(c.tlist.ptr, tl.data(), tl.size() * sizeof(int), hipMemcpyHostToDevice, c.stream));
+        HIPC(hipMemcpyAsync(c.tlist.ptr, c.tlist_h.data(), tl.size() * sizeof(int), hipMemcpyHostToDevice, c.stream));
         c.lists_pending = true;
     }
     if (!F.pairs.empty()) fmm_setup(c, cb0, cb1);
