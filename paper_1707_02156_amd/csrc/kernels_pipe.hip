@@ -231,16 +231,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // DL: Fa^mu[j'][t*12 + pair*2 + {cos, sin}] of the six stresslet fields.
 //
 // The Fourier sums are contractions on v_mfma_f64_4x4x4 (four blocks of 4x4x4:
-// 4 rows x 16 columns x depth 4, the granule that wastes least for 9 to 28
-// rows) with the symmetries of the longitudes folded in: with the even and odd
+// 4 rows x 16 columns x depth 4) with the symmetries of the longitudes folded in: with the even and odd
 // orders and the cosine and sine sums apart, row kk <= qs/2 gives the points
 // kk, kk + qs, -kk and qs - kk, a quarter of the plain product's work. Columns
 // are the item's 16 targets, so the three components of x, x_theta, x_phi and
 // f at a point meet in one lane, which evaluates the pole rule at its points
 // and holds the folded stresslet values as operand rows of the analysis.
 //
-// A wavefront takes two row tiles: each LDS read feeds both, and the 48 or 24
-// independent products of a step cover its latency (one tile per wavefront at
+// A wavefront takes two row tiles, so that rows are padded to eights (9 of degree
+// 16 to 16, 17 of degree 32 to 24, 25 of degree 48 to 32: an empty tile runs):
+// each LDS read feeds both, and the 48 or 24 independent products of a step cover
+// its latency (one tile per wavefront at
 // four wavefronts per SIMD read twice as much and waited: 2.26 ms against 2.05
 // at the size below). A block (2 to 4 wavefronts, 79 KB of LDS at p = 48, two
 // per CU) walks over items; the slab of G that is summed next is on its way
